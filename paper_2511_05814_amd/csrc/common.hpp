@@ -108,15 +108,41 @@ struct PrefillPlan {
   int32_t pad[3];
 };
 
-struct GemmJob {
+// A tile of a grouped GEMM: `rows` sorted rows from `row` on, all of the
+// expert whose weights are at w, by the output columns from n0 on.
+struct GemmTile {
   const uint16_t *w;  // expert base (W1 | W3 | W2), bf16
-  int32_t row0;       // first sorted row of the expert
-  int32_t nrows;      // rows routed to it
+  int32_t row, rows, n0, pad;
+};
+constexpr int kWideRows = 256, kNarrowRows = 64;  // most rows of a wide and of a narrow tile
+
+// How a launch's tiles are cut: column blocks of `cols` output columns, row
+// blocks of 32 * k rows with lo <= 32 * k <= hi (the plan chooses k), at most
+// `cap` tiles in all.
+struct TileList {
+  int cols, cb, lo, hi, first, cap;
 };
 
-struct GemmTile {
-  int32_t job, m0, n0, pad;
-};
+// Relative cost of a launch of `tiles` tiles whose row blocks number `blocks`
+// 32-row blocks in all, on `cus` compute units.  A tile costs its staging of
+// the weights (2.6 row blocks' worth) and its row blocks; a last round that
+// fills only part of the units costs half a round and half its share.  Fitted
+// on MI355X to 2048 tokens of top-2 over 8 experts (down, d_ff 14336), row
+// blocks of 96 .. 256: 592, 638, 538, 579, 615, 622 us measured, 610, 638,
+// 543, 574, 584, 635 by the model.
+__host__ __device__ inline float tile_cost(int tiles, int blocks, int cus) {
+  if (tiles <= 0) return 0.0f;
+  const float n = (float)tiles / (float)cus;
+  const float rounds = 0.5f * ((float)((tiles + cus - 1) / cus) + n);
+  return rounds / n * (2.6f * (float)tiles + (float)blocks);
+}
+
+// Rows of an expert's tiles when its n > 0 rows are cut into blocks of at most
+// r rows: equal blocks, rounded up to 32.
+__host__ __device__ inline int tile_rows(int n, int r) {
+  const int nt = (n + r - 1) / r;
+  return ((n + nt - 1) / nt + 31) / 32 * 32;
+}
 
 struct PrefillArgs {
   const void *gate;  // layer's gate [E][d]
@@ -144,16 +170,14 @@ struct PlanArgs {
   int T, K, E, S, layer, policy;
   int aging;  // aged LFU: lookup-clock ticks per halving of a count
   // Batches planned on the device (a slot for every expert): the kernel also
-  // writes one GEMM job per expert; nullptr otherwise.  Small batches
-  // (ntiles == nullptr) take one small-M tile per expert.  Large ones take
-  // tile lists of tile_rows rows by up_cols / dn_cols columns, ordered (expert,
-  // column block, row block): the up list at tiles[0 ..], the down list at
-  // tiles[dn_first ..], at most up_cap and dn_cap tiles, their lengths
-  // written to ntiles[0] and ntiles[1].
-  GemmJob *jobs;
+  // writes the GEMM tiles; nullptr otherwise.  Small batches (ntiles ==
+  // nullptr) take one small-M tile per expert.  Others take two lists ordered
+  // (expert, column block, row block): the up list at tiles[0 ..], the down
+  // list at tiles[dn.first ..], their lengths written to ntiles[0] and [1].
   GemmTile *tiles;
   int32_t *ntiles;
-  int tile_rows, up_cols, dn_cols, up_cb, dn_cb, dn_first, up_cap, dn_cap;
+  TileList up, dn;
+  int cus;  // compute units the tiles are spread over
   const uint8_t *arena_layer;  // this layer's slots
   uint64_t slot_bytes;
 };
@@ -208,28 +232,24 @@ hipError_t launch_ffnq_down(const FfnArgs &a, const Launch &l);
 int ffnq_down_chunks(int K, int d_ff);
 hipError_t launch_prefill_gate(const PrefillArgs &a, const Launch &l);
 hipError_t launch_prefill_plan(const PlanArgs &a, const Launch &l);
-// grouped GEMMs over tiles of `rows` (64, 128 or 256) sorted pairs by
-// prefill_tile_cols(up) output columns; a_bytes: size of the A operand's
-// buffer (xn for up, act for down).  With dev_ntiles, the list's length is
-// read on the device (at most ntiles, the grid; the surplus workgroups exit).
-hipError_t launch_prefill_up(const GemmTile *tiles, int ntiles, const GemmJob *jobs, const uint16_t *xn,
-                             const int32_t *perm_tok, uint16_t *act, int d, int d_ff, int rows, size_t a_bytes,
-                             const Launch &l, const int32_t *dev_ntiles = nullptr);
-// Small-M grouped GEMMs: one tile {job, 0, 0} per expert, each with at most
-// max_rows <= kSkinnyRows rows (the caller's bound: rows beyond 16 are read
-// only when max_rows > 16); a workgroup per (tile, 16 output features).
-constexpr int kSkinnyRows = 32;
-hipError_t launch_prefill_skinny_up(const GemmTile *tiles, int ntiles, const GemmJob *jobs, const uint16_t *xn,
-                                    const int32_t *perm_tok, uint16_t *act, int d, int d_ff, int max_rows,
-                                    const Launch &l);
-hipError_t launch_prefill_skinny_down(const GemmTile *tiles, int ntiles, const GemmJob *jobs, const uint16_t *act,
-                                      float *Y, int d, int d_ff, int max_rows, const Launch &l);
-hipError_t launch_prefill_down(const GemmTile *tiles, int ntiles, const GemmJob *jobs, const uint16_t *act,
-                               float *Y, int d, int d_ff, int rows, size_t a_bytes, const Launch &l,
-                               const int32_t *dev_ntiles = nullptr);
+// Grouped GEMMs over a tile list (wide tiles: up to kWideRows rows by
+// prefill_tile_cols(up, true) output columns; narrow ones up to kNarrowRows by
+// half as many).  With ntiles the list's length is read on the device (at most
+// `grid`; the surplus workgroups exit), otherwise it is `grid`.
+hipError_t launch_prefill_up(const GemmTile *tiles, const int32_t *ntiles, int grid, bool wide, const uint16_t *xn,
+                             const int32_t *perm_tok, uint16_t *act, int d, int d_ff, const Launch &l);
+hipError_t launch_prefill_down(const GemmTile *tiles, const int32_t *ntiles, int grid, bool wide, const uint16_t *act,
+                               float *Y, int d, int d_ff, const Launch &l);
+constexpr int prefill_tile_cols(bool up, bool wide) { return (up ? 128 : 256) / (wide ? 1 : 2); }
+// Small-M grouped GEMMs: one tile per expert, each with at most kSkinnyRows
+// rows; a workgroup per (tile, 16 output features).
+constexpr int kSkinnyRows = 16;
+hipError_t launch_prefill_skinny_up(const GemmTile *tiles, int ntiles, const uint16_t *xn, const int32_t *perm_tok,
+                                    uint16_t *act, int d, int d_ff, const Launch &l);
+hipError_t launch_prefill_skinny_down(const GemmTile *tiles, int ntiles, const uint16_t *act, float *Y, int d, int d_ff,
+                                      const Launch &l);
 hipError_t launch_prefill_unpermute(float *H, const float *Y, const float *g, const int32_t *pos_of, int T,
                                     int d, int K, const Launch &l);
-int prefill_tile_cols(bool up);  // GEMM output tile columns (act for up, Y for down)
 
 // ---------------------------------------------------------------------------
 // device helpers

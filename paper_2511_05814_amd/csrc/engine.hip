@@ -159,7 +159,7 @@ hipError_t scratch_on_device(int dev, uint8_t **out) {
 namespace moe {
 // Prefill workspace for batches of up to T tokens (offsets from its base).
 struct PrefillLayout {
-  size_t ids = 0, g = 0, inv_r = 0, xn = 0, perm = 0, pos = 0, plan = 0, jobs = 0, tiles = 0, act = 0,
+  size_t ids = 0, g = 0, inv_r = 0, xn = 0, perm = 0, pos = 0, plan = 0, tiles = 0, act = 0,
          y = 0, staging = 0, coded = 0, lists = 0, ntiles = 0, total = 0;
   int tile_cap = 0;  // GEMM tiles the schedule can hold
   int ring = 0;      // staging slots for experts streamed through the batch
@@ -179,8 +179,9 @@ static PrefillLayout prefill_layout(int K, int d, int d_ff, int E, int S, int T,
     return at;
   };
   const size_t P = (size_t)T * K;
-  const int rows = 64;
-  p.tile_cap = (int)((P + rows - 1) / rows + E) * ((d_ff + rows - 1) / rows + (d + rows - 1) / rows);
+  // every expert cut into the shortest row blocks and the narrowest columns
+  const int up_cols = prefill_tile_cols(true, false), dn_cols = prefill_tile_cols(false, false);
+  p.tile_cap = (int)((P + 31) / 32 + E) * ((d_ff + up_cols - 1) / up_cols + (d + dn_cols - 1) / dn_cols);
   int half = (E - S + 1) / 2;
   half = half < 1 ? 1 : (half > 4 ? 4 : half);
   p.ring = 2 * half;
@@ -191,7 +192,6 @@ static PrefillLayout prefill_layout(int K, int d, int d_ff, int E, int S, int T,
   p.perm = take(P * 4);
   p.pos = take(P * 4);
   p.plan = take(sizeof(PrefillPlan) * kMaxE);
-  p.jobs = take(sizeof(GemmJob) * kMaxE);
   p.tiles = take(sizeof(GemmTile) * (size_t)p.tile_cap);
   p.act = take(P * d_ff * 2);
   p.y = take(P * d * 4);
@@ -250,7 +250,7 @@ struct moe_cache {
   // batched prefill
   PrefillLayout play;
   PrefillPlan *h_plan = nullptr;   // pinned: plan of the last prefill layer
-  uint8_t *h_sched = nullptr;      // pinned: GEMM jobs + tiles uploaded per layer
+  uint8_t *h_sched = nullptr;      // pinned: GEMM tiles uploaded per layer
   std::vector<hipEvent_t> pf_ev;   // prefill ordering events
   // kernel timing (moe_cache_set_timing)
   int timing = MOE_TIMING_OFF;
@@ -578,8 +578,7 @@ int moe_cache_bind(moe_cache_t *c, const moe_model_desc *d) {
     HIP_TRY0(pool_pinned(c->dev, sizeof(PrefillPlan) * kMaxE + sizeof(int32_t), reinterpret_cast<void **>(&c->h_plan),
                          &c->plan_bytes));
     HIP_TRY0(pool_pinned(c->dev,
-                         sizeof(GemmJob) * kMaxE + sizeof(GemmTile) * (size_t)c->play.tile_cap +
-                             sizeof(FetchList) * kPrefillLists,
+                         sizeof(GemmTile) * (size_t)c->play.tile_cap + sizeof(FetchList) * kPrefillLists,
                          reinterpret_cast<void **>(&c->h_sched), &c->sched_bytes));
     c->pf_ev.assign(2 * kMaxE + 4, nullptr);
     for (auto &e : c->pf_ev) HIP_TRY0(pool_event(c->dev, false, &e));
@@ -881,8 +880,6 @@ static int enqueue_layer(moe_cache *c, int layer, float *h, const int32_t *inj, 
 
 namespace moe {
 
-constexpr int kTallRows = 256;  // rows of a device-planned tile
-
 // compute units of the handle's device (read once)
 static int device_cus(moe_cache *c) {
   if (c->cus <= 0) {
@@ -896,6 +893,31 @@ static int device_cus(moe_cache *c) {
   return c->cus;
 }
 
+// How the grouped GEMM that writes `ncols` output columns is cut when
+// `experts` experts have `pairs` rows between them.  Narrow tiles where wide
+// ones would leave compute units without a tile and the experts have few rows
+// each (8 experts, d_ff 14336, down, us with wide / narrow tiles: 32 tokens of
+// top-2 220 / 174, 128 tokens 228 / 174, 256 tokens 246 / 253; with 64 experts
+// of d 2048 there are enough wide tiles and the two are equal).  The shortest
+// row blocks a plan may choose are those that a launch sized for any routing
+// can hold with at most two surplus workgroups a compute unit.
+static TileList tile_list(bool up, int ncols, long pairs, int experts, int cus, bool *wide) {
+  const int wide_cols = prefill_tile_cols(up, true);
+  *wide = (long)((ncols + wide_cols - 1) / wide_cols) * experts >= cus || pairs > 48L * experts;
+  TileList t{};
+  t.cols = prefill_tile_cols(up, *wide);
+  t.cb = (ncols + t.cols - 1) / t.cols;
+  t.hi = *wide ? kWideRows : kNarrowRows;
+  // tiles of at most r rows: an expert with n > 0 rows has at most
+  // 1 + (n - 1) / r of them per column block
+  const long m = std::min<long>(experts, pairs);
+  auto most = [&](int r) { return t.cb * (m + (pairs - m) / r); };
+  t.lo = t.hi;
+  while (t.lo > 32 && most(t.lo - 32) <= most(t.hi) + 2L * cus) t.lo -= 32;
+  t.cap = (int)most(t.lo);
+  return t;
+}
+
 // Batched prefill of one layer.  Routing and the cache decision run on the
 // device; the host then waits for the plan (a few hundred bytes), because it
 // has to issue one copy per streamed expert and size the grouped GEMMs:
@@ -907,8 +929,8 @@ static int device_cus(moe_cache *c) {
 //   copy:    newcomers nobody routed (wait A) -> event F; compute waits F
 //   compute: unpermute (h += sum_r g Y)
 // With a slot for every expert nothing is streamed, and the plan kernel also
-// plans the GEMMs (one small-M tile per expert for small batches, the tall
-// tile lists for large ones), so the host waits for nothing.
+// plans the GEMMs (one small-M tile per expert for small batches, two tile
+// lists for others), so the host waits for nothing.
 int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   const PrefillLayout &p = c->play;
   uint8_t *base = c->prefill_ws;
@@ -919,7 +941,6 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   int32_t *perm = reinterpret_cast<int32_t *>(base + p.perm);
   int32_t *pos = reinterpret_cast<int32_t *>(base + p.pos);
   PrefillPlan *plan = reinterpret_cast<PrefillPlan *>(base + p.plan);
-  GemmJob *jobs = reinterpret_cast<GemmJob *>(base + p.jobs);
   GemmTile *tiles = reinterpret_cast<GemmTile *>(base + p.tiles);
   uint16_t *act = reinterpret_cast<uint16_t *>(base + p.act);
   float *Y = reinterpret_cast<float *>(base + p.y);
@@ -963,63 +984,44 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   pa.layer = layer;
   pa.policy = c->policy;
   pa.aging = c->policy == MOE_POLICY_LFU_AGED ? c->desc.aging_ticks : 0;
-  // With a slot for every expert nothing is ever streamed, and with at most
-  // kSkinnyRows tokens every expert's rows fit the small-M GEMMs: the plan
-  // kernel then writes the GEMM jobs itself and the host does not wait for it.
-  const bool device_plan = c->S == c->E && T <= kSkinnyRows;
-  // A larger batch with a slot for every expert, when 256-row tiles give every
-  // CU two tiles whatever the routing (the rule the host applies below picks
-  // them then): the plan kernel writes both tile lists and the GEMMs read
-  // their lengths, so the host waits for nothing.  The grids cover the longest
-  // lists any routing can give.
-  const int up_cols = prefill_tile_cols(true), down_cols = prefill_tile_cols(false);
-  const int up_cb = (c->dff + up_cols - 1) / up_cols, dn_cb = (c->d + down_cols - 1) / down_cols;
+  // With a slot for every expert nothing is ever streamed: the plan kernel
+  // writes the GEMM tiles itself and the host does not wait for it.  Batches
+  // of at most kSkinnyRows tokens take the small-M GEMMs (every expert's rows
+  // fit them), others two tile lists whose lengths the GEMMs read on the
+  // device; the grids cover the longest lists any routing can give.
+  const bool on_device = c->S == c->E, skinny_plan = on_device && T <= kSkinnyRows;
+  const int cus = device_cus(c);
   const long pairs = (long)T * c->K;
-  const int tall_cap_rows = (int)((pairs + kTallRows - 1) / kTallRows) + c->E;  // bounds the sum of ceil(n_e / rows)
-  const int up_cap = tall_cap_rows * up_cb, dn_cap = tall_cap_rows * dn_cb;
-  const bool device_tall = c->S == c->E && !device_plan && (pairs / kTallRows) * std::min(up_cb, dn_cb) >= 2L * device_cus(c) &&
-                           up_cap + dn_cap <= p.tile_cap;
   int32_t *dev_ntiles = reinterpret_cast<int32_t *>(base + p.ntiles);
-  pa.jobs = device_plan || device_tall ? jobs : nullptr;
-  pa.tiles = device_plan || device_tall ? tiles : nullptr;
-  pa.ntiles = device_tall ? dev_ntiles : nullptr;
-  pa.tile_rows = kTallRows;
-  pa.up_cols = up_cols;
-  pa.dn_cols = down_cols;
-  pa.up_cb = up_cb;
-  pa.dn_cb = dn_cb;
-  pa.dn_first = up_cap;
-  pa.up_cap = up_cap;
-  pa.dn_cap = dn_cap;
+  bool up_wide = true, dn_wide = true;
+  pa.tiles = on_device ? tiles : nullptr;
+  pa.ntiles = on_device && !skinny_plan ? dev_ntiles : nullptr;
+  pa.up = tile_list(true, c->dff, pairs, c->E, cus, &up_wide);
+  pa.dn = tile_list(false, c->d, pairs, c->E, cus, &dn_wide);
+  pa.dn.first = pa.up.cap;
+  pa.cus = cus;
+  if (pa.ntiles && pa.up.cap + pa.dn.cap > p.tile_cap) {  // cannot happen: the capacity counts the shortest, narrowest tiles
+    c->sticky = MOE_ERR_HIP;
+    return fail(MOE_ERR_HIP, "prefill tile schedule overflow (capacity %d)", p.tile_cap);
+  }
   pa.arena_layer = arena + (size_t)layer * c->S * c->B;
   pa.slot_bytes = c->B;
   HIP_TRY(c, launch_prefill_plan(pa, Launch{c->cs}));
   c->tpar ^= 1;
-  if (device_tall) {
+  if (on_device) {
     const double rows = (double)pairs;
     Launch lu, ld;
     HIP_TRY(c, kernel_span(c, c->cs, &lu, SPAN_GEMM_UP));
-    HIP_TRY(c, launch_prefill_up(tiles, up_cap, jobs, xn, perm, act, c->d, c->dff, kTallRows, (size_t)c->max_T * c->d * 2, lu,
-                                 dev_ntiles));
+    if (skinny_plan)
+      HIP_TRY(c, launch_prefill_skinny_up(tiles, c->E, xn, perm, act, c->d, c->dff, lu));
+    else
+      HIP_TRY(c, launch_prefill_up(tiles, dev_ntiles, pa.up.cap, up_wide, xn, perm, act, c->d, c->dff, lu));
     kernel_span_done(c, SPAN_GEMM_UP, lu, rows * 4.0 * c->d * c->dff);
     HIP_TRY(c, kernel_span(c, c->cs, &ld, SPAN_GEMM_DOWN));
-    HIP_TRY(c, launch_prefill_down(tiles + up_cap, dn_cap, jobs, act, Y, c->d, c->dff, kTallRows,
-                                   (size_t)c->max_T * c->K * c->dff * 2, ld, dev_ntiles + 1));
-    kernel_span_done(c, SPAN_GEMM_DOWN, ld, rows * 2.0 * c->d * c->dff);
-    HIP_TRY(c, launch_prefill_unpermute(H, Y, g, pos, T, c->d, c->K, Launch{c->cs}));
-    HIP_TRY(c, span_end(c, c->cs, SPAN_PREFILL, tp));
-    c->last_route_kind = 2;
-    c->last_prefill_T = T;
-    return MOE_OK;  // routing errors surface at the next synchronising call
-  }
-  if (device_plan) {
-    const double rows = (double)T * c->K;
-    Launch lu, ld;
-    HIP_TRY(c, kernel_span(c, c->cs, &lu, SPAN_GEMM_UP));
-    HIP_TRY(c, launch_prefill_skinny_up(tiles, c->E, jobs, xn, perm, act, c->d, c->dff, T, lu));
-    kernel_span_done(c, SPAN_GEMM_UP, lu, rows * 4.0 * c->d * c->dff);
-    HIP_TRY(c, kernel_span(c, c->cs, &ld, SPAN_GEMM_DOWN));
-    HIP_TRY(c, launch_prefill_skinny_down(tiles, c->E, jobs, act, Y, c->d, c->dff, T, ld));
+    if (skinny_plan)
+      HIP_TRY(c, launch_prefill_skinny_down(tiles, c->E, act, Y, c->d, c->dff, ld));
+    else
+      HIP_TRY(c, launch_prefill_down(tiles + pa.dn.first, dev_ntiles + 1, pa.dn.cap, dn_wide, act, Y, c->d, c->dff, ld));
     kernel_span_done(c, SPAN_GEMM_DOWN, ld, rows * 2.0 * c->d * c->dff);
     HIP_TRY(c, launch_prefill_unpermute(H, Y, g, pos, T, c->d, c->K, Launch{c->cs}));
     HIP_TRY(c, span_end(c, c->cs, SPAN_PREFILL, tp));
@@ -1043,11 +1045,11 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   c->last_route_kind = 2;
   c->last_prefill_T = T;
 
-  // jobs: weights of every routed expert, where the GEMMs will find them
+  // weights of every routed expert, where the GEMMs will find them
   const int E = c->E;
   const PrefillPlan *pl = c->h_plan;
-  GemmJob *hj = reinterpret_cast<GemmJob *>(c->h_sched);
-  GemmTile *ht = reinterpret_cast<GemmTile *>(c->h_sched + sizeof(GemmJob) * kMaxE);
+  const uint16_t *weights[kMaxE] = {};
+  GemmTile *ht = reinterpret_cast<GemmTile *>(c->h_sched);
   std::vector<int> resident, streamed, unrouted_new;
   for (int e = 0; e < E; ++e) {
     if (pl[e].n < 0 || pl[e].off < 0 || pl[e].off + pl[e].n > T * c->K || pl[e].slot_start >= c->S ||
@@ -1055,12 +1057,9 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
       c->sticky = MOE_ERR_HIP;
       return fail(MOE_ERR_HIP, "inconsistent prefill plan from the device");
     }
-    hj[e].w = nullptr;
-    hj[e].row0 = pl[e].off;
-    hj[e].nrows = pl[e].n;
     if (pl[e].n > 0 && pl[e].slot_start >= 0) {
       resident.push_back(e);
-      hj[e].w = reinterpret_cast<const uint16_t *>(arena + ((size_t)layer * c->S + pl[e].slot_start) * c->B);
+      weights[e] = reinterpret_cast<const uint16_t *>(arena + ((size_t)layer * c->S + pl[e].slot_start) * c->B);
     } else if (pl[e].n == 0 && pl[e].newcomer) {
       unrouted_new.push_back(e);
     }
@@ -1079,46 +1078,57 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
     int used = 0;
     for (int e : batches[bi]) {
       if (pl[e].slot_after >= 0) {
-        hj[e].w = reinterpret_cast<const uint16_t *>(arena + ((size_t)layer * c->S + pl[e].slot_after) * c->B);
+        weights[e] = reinterpret_cast<const uint16_t *>(arena + ((size_t)layer * c->S + pl[e].slot_after) * c->B);
       } else {
         ring_of[e] = (int)(bi % 2) * half + used++;
-        hj[e].w = reinterpret_cast<const uint16_t *>(staging + (size_t)ring_of[e] * c->B);
+        weights[e] = reinterpret_cast<const uint16_t *>(staging + (size_t)ring_of[e] * c->B);
       }
     }
   }
-  // Output tiles of 256, 128 or 64 rows (sorted pairs) by 128 (up) or 256
-  // (down) columns: the
-  // tallest that still gives every CU two tiles (256-row tiles run one
-  // 512-lane workgroup per CU, the others two or three of 256 lanes).  Within
-  // an expert the tiles of one column block are consecutive, so a column
-  // block's weights are read once for all of the expert's row blocks by
-  // workgroups that run at the same time on one XCD (the kernel hands each
-  // XCD a contiguous stretch of this list).
-  const int cus = device_cus(c);
+  // Tiles of one group's launch.  Within an expert the tiles of one column
+  // block are consecutive, so a column block's weights are read once for all
+  // of the expert's row blocks by workgroups that run at the same time on one
+  // XCD (the kernel hands each XCD a contiguous stretch of this list).
   int nt = 0;
   bool overflow = false;  // checked before each write: ht is a fixed-size pinned buffer
-  auto add_tiles = [&](const std::vector<int> &group, int ncols, int cols, int &first, int &count, int &rows) {
-    auto tiles_of = [&](int r) {
-      long n = 0;
-      for (int e : group) n += (long)((pl[e].n + r - 1) / r) * ((ncols + cols - 1) / cols);
-      return n;
-    };
-    rows = tiles_of(256) >= 2L * cus ? 256 : (tiles_of(128) >= 2L * cus ? 128 : 64);
+  auto add_tile = [&](int e, int m0, int rows, int n0) {
+    if (nt >= p.tile_cap)
+      overflow = true;
+    else
+      ht[nt++] = GemmTile{weights[e], pl[e].off + m0, rows, n0, 0};
+  };
+  auto add_tiles = [&](const std::vector<int> &group, long rows, bool up, int &first, int &count, bool &wide) {
+    const int ncols = up ? c->dff : c->d;
+    const TileList tl = tile_list(up, ncols, rows, (int)group.size(), cus, &wide);
+    int best = tl.hi;
+    float best_cost = 0.0f;
+    for (int r = tl.hi; r >= tl.lo; r -= 32) {
+      long n = 0, blocks = 0;
+      for (int e : group) {
+        const int per = tile_rows(pl[e].n, r), k = (pl[e].n + per - 1) / per;
+        n += k;
+        blocks += (long)k * (per / 32);
+      }
+      const float cost = tile_cost((int)(tl.cb * n), (int)(tl.cb * blocks), cus);
+      if (r == tl.hi || cost < best_cost) {
+        best = r;
+        best_cost = cost;
+      }
+    }
     first = nt;
-    for (int e : group)
-      for (int n0 = 0; n0 < ncols; n0 += cols)
-        for (int m0 = 0; m0 < pl[e].n; m0 += rows) {
-          if (nt >= p.tile_cap) {
-            overflow = true;
-            continue;
-          }
-          ht[nt++] = GemmTile{e, m0, n0, 0};
-        }
+    for (int e : group) {
+      const int per = tile_rows(pl[e].n, best);
+      for (int n0 = 0; n0 < ncols; n0 += tl.cols)
+        for (int m0 = 0; m0 < pl[e].n; m0 += per) add_tile(e, m0, std::min(per, pl[e].n - m0), n0);
+    }
     count = nt - first;
   };
   const size_t ngroups = batches.size() + 1;
-  std::vector<int> up_first(ngroups), up_n(ngroups), dn_first(ngroups), dn_n(ngroups), up_rows(ngroups),
-      dn_rows(ngroups), skinny(ngroups, 0);
+  std::vector<int> up_first(ngroups), up_n(ngroups), dn_first(ngroups), dn_n(ngroups);
+  struct GroupKind {
+    bool skinny = false, up_wide = true, dn_wide = true;
+  };
+  std::vector<GroupKind> kind(ngroups);
   std::vector<double> group_rows(ngroups, 0.0);
   // a group whose experts all have few rows (batched decode) goes to the
   // small-M kernels: one tile per expert, shared by the up and down launches
@@ -1129,24 +1139,18 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
       group_rows[gi] += pl[e].n;
     }
     if (most <= kSkinnyRows) {
-      skinny[gi] = std::max(most, 1);  // the group's largest row count
+      kind[gi].skinny = true;
       up_first[gi] = dn_first[gi] = nt;
-      for (int e : group) {
-        if (nt >= p.tile_cap) {
-          overflow = true;
-          continue;
-        }
-        ht[nt++] = GemmTile{e, 0, 0, 0};
-      }
+      for (int e : group) add_tile(e, 0, pl[e].n, 0);
       up_n[gi] = dn_n[gi] = nt - up_first[gi];
     } else {
-      add_tiles(group, c->dff, up_cols, up_first[gi], up_n[gi], up_rows[gi]);
-      add_tiles(group, c->d, down_cols, dn_first[gi], dn_n[gi], dn_rows[gi]);
+      add_tiles(group, (long)group_rows[gi], true, up_first[gi], up_n[gi], kind[gi].up_wide);
+      add_tiles(group, (long)group_rows[gi], false, dn_first[gi], dn_n[gi], kind[gi].dn_wide);
     }
   };
   add_group(resident, 0);
   for (size_t bi = 0; bi < batches.size(); ++bi) add_group(batches[bi], bi + 1);
-  if (overflow) {  // cannot happen: the capacity counts 64 x 64 tiles
+  if (overflow) {  // cannot happen: the capacity counts the shortest, narrowest tiles
     c->sticky = MOE_ERR_HIP;
     return fail(MOE_ERR_HIP, "prefill tile schedule overflow (capacity %d)", p.tile_cap);
   }
@@ -1162,8 +1166,7 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   };
   std::vector<std::vector<Part>> batch_parts(batches.size());
   std::vector<Part> unrouted_parts;
-  FetchList *hl = reinterpret_cast<FetchList *>(c->h_sched + sizeof(GemmJob) * kMaxE +
-                                                sizeof(GemmTile) * (size_t)p.tile_cap);
+  FetchList *hl = reinterpret_cast<FetchList *>(c->h_sched + sizeof(GemmTile) * (size_t)p.tile_cap);
   FetchList *dlists = reinterpret_cast<FetchList *>(base + p.lists);
   int nl = 0;
   auto add_part = [&](std::vector<Part> &parts, const std::vector<int> &ex, bool ring) {
@@ -1202,10 +1205,7 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
     c->sticky = MOE_ERR_HIP;
     return fail(MOE_ERR_HIP, "prefill fetch-list overflow");
   }
-  // the jobs and the tiles after them, in one copy: the two lie back to back
-  // in the pinned schedule and in the workspace
-  static_assert(sizeof(GemmJob) * kMaxE % 256 == 0, "tiles follow the jobs in the workspace");
-  HIP_TRY(c, hipMemcpyAsync(jobs, hj, sizeof(GemmJob) * kMaxE + sizeof(GemmTile) * nt, hipMemcpyHostToDevice, c->cs));
+  HIP_TRY(c, hipMemcpyAsync(tiles, ht, sizeof(GemmTile) * nt, hipMemcpyHostToDevice, c->cs));
   if (nl > 0) HIP_TRY(c, hipMemcpyAsync(dlists, hl, sizeof(FetchList) * nl, hipMemcpyHostToDevice, c->cs));
 
   const double up_flop_per_row = 4.0 * c->d * c->dff, down_flop_per_row = 2.0 * c->d * c->dff;
@@ -1213,19 +1213,16 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
     if (up_n[gi] <= 0) return MOE_OK;
     Launch lu, ld;
     HIP_TRY(c, kernel_span(c, c->cs, &lu, SPAN_GEMM_UP));
-    if (skinny[gi])
-      HIP_TRY(c, launch_prefill_skinny_up(tiles + up_first[gi], up_n[gi], jobs, xn, perm, act, c->d, c->dff,
-                                            skinny[gi], lu));
+    if (kind[gi].skinny)
+      HIP_TRY(c, launch_prefill_skinny_up(tiles + up_first[gi], up_n[gi], xn, perm, act, c->d, c->dff, lu));
     else
-      HIP_TRY(c, launch_prefill_up(tiles + up_first[gi], up_n[gi], jobs, xn, perm, act, c->d, c->dff, up_rows[gi],
-                                   (size_t)c->max_T * c->d * 2, lu));
+      HIP_TRY(c, launch_prefill_up(tiles + up_first[gi], nullptr, up_n[gi], kind[gi].up_wide, xn, perm, act, c->d, c->dff, lu));
     kernel_span_done(c, SPAN_GEMM_UP, lu, group_rows[gi] * up_flop_per_row);
     HIP_TRY(c, kernel_span(c, c->cs, &ld, SPAN_GEMM_DOWN));
-    if (skinny[gi])
-      HIP_TRY(c, launch_prefill_skinny_down(tiles + dn_first[gi], dn_n[gi], jobs, act, Y, c->d, c->dff, skinny[gi], ld));
+    if (kind[gi].skinny)
+      HIP_TRY(c, launch_prefill_skinny_down(tiles + dn_first[gi], dn_n[gi], act, Y, c->d, c->dff, ld));
     else
-      HIP_TRY(c, launch_prefill_down(tiles + dn_first[gi], dn_n[gi], jobs, act, Y, c->d, c->dff, dn_rows[gi],
-                                     (size_t)c->max_T * c->K * c->dff * 2, ld));
+      HIP_TRY(c, launch_prefill_down(tiles + dn_first[gi], nullptr, dn_n[gi], kind[gi].dn_wide, act, Y, c->d, c->dff, ld));
     kernel_span_done(c, SPAN_GEMM_DOWN, ld, group_rows[gi] * down_flop_per_row);
     return MOE_OK;
   };

@@ -1,0 +1,343 @@
+// Grouped GEMMs of the batched paths (prefill and batched decode of more than
+// a handful of rows): rows sorted by expert times that expert's weights.
+//
+//   up    act[row] = SiLU(W1 x) * (W3 x), x = xn[perm_tok[row]]   (bf16 out)
+//   down  Y[row]   = W2 act[row]                                   (fp32 out)
+//
+// Weights are stored out x in, so both operands are K-major.  A tile is up to
+// 256 sorted rows of one expert by 256 weight rows (128 output features of W1
+// and of W3 in the up projection, 256 of W2 in the down projection; half as
+// many in the narrow form).  Four waves, one a SIMD: each owns a quarter of
+// the weight rows and all MX 32-row blocks of the tile (MX = 1 .. 8 is a
+// template parameter, so a tile costs what its rows need, to 32 rows).
+//
+// Both operands are staged by the memory system (loads straight into LDS) in
+// slices of 64 columns, whole 128-byte lines, into rings of three slices (two
+// of weights when the tile has more than 160 rows: 160 KB of LDS).  A wave
+// keeps the fragments of the next 16-deep part in registers while it
+// multiplies the current one, and the one barrier per slice stands before the
+// last part's products, so the matrix cores have work queued while the waves
+// meet.  The loads are dealt out between the products, one every two to four:
+// issued back to back they fill the address path and stall the wave.
+//
+// Measured on MI355X (us, up / down): 4096 tokens of top-8 over 64 experts, d
+// 2048, d_ff 1408: 430 / 258 (eight waves of 64-row slabs, two slices, no
+// fragment prefetch: 423-489 / 249-270); 2048 tokens of top-2 over 8 experts,
+// d 4096, d_ff 14336: 915 / 515 (1011-1121 / 803-860).  Without its loads the
+// same loop takes 744 and without any operand traffic 686 of those 915, and
+// 76 of the 258 are the drain of the 268 MB result.
+#include "common.hpp"
+
+#include <type_traits>
+
+namespace moe {
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void lds_void_t;
+
+constexpr int kThreads = 256;
+constexpr int kKs = 64;            // columns of a slice
+constexpr int kRowB = kKs * 2;     // bytes of a slice row: one 128-byte line
+constexpr int kBlockB = 32 * kRowB;  // bytes of 32 slice rows
+// Byte offset for a chunk that must read zeros: at or past every weight
+// resource's record count (all below 2^31), which the hardware turns into
+// zeros.  The range check admits any dword that starts below the record
+// count, so the offset must clear it, not merely approach it.
+constexpr uint32_t kOobOffset = 0x80000000u;
+
+__device__ const uint4 g_zeros[1] = {};  // what rows of A read past the end of K
+
+__device__ __forceinline__ uint32_t bf16_rne(float f) {
+  uint32_t u = __float_as_uint(f);
+  u += 0x7FFFu + ((u >> 16) & 1u);
+  return u >> 16;
+}
+
+// v / (1 + e^-v) with the hardware's exponential and reciprocal (one ulp
+// each); the result is rounded to bf16.
+__device__ __forceinline__ float silu(float v) {
+  return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * -1.44269504088896340736f));
+}
+
+// One wave-wide 16-byte-a-lane load into LDS at m0 + 16 * lane.  Written as
+// instructions of their own rather than the compiler's builtin: the compiler
+// tracks loads in flight into LDS per array, loses track across a ring's loop
+// and then waits for all of them before reading any slice; here the kernel's
+// own waits (wait_vm) are the only ones.  M0 carries the LDS address; the
+// compiler sets M0 itself before any instruction of its own that reads it
+// (none in this kernel: gfx9 LDS instructions do not use it).
+__device__ __forceinline__ void dma_weights(__amdgpu_buffer_rsrc_t r, uint32_t m0, uint32_t voff, uint32_t soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               : : "s"(__builtin_amdgcn_readfirstlane(m0)), "v"(voff), "s"(r), "s"(__builtin_amdgcn_readfirstlane(soff)) : "memory");
+}
+__device__ __forceinline__ void dma_rows(const void *p, uint32_t m0) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               : : "s"(__builtin_amdgcn_readfirstlane(m0)), "v"(p) : "memory");
+}
+
+// s_waitcnt with vmcnt = N, or lgkmcnt = 0, and the other counters left alone
+// (gfx9 encoding)
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt field");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
+}
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (0x7 << 4)); }
+
+__device__ __forceinline__ bf16x8 frag(const uint8_t *p) {
+  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(p));
+}
+
+// One tile of MX 32-row blocks by NY * 128 weight rows, in an LDS area of
+// LDS bytes.  A slice row holds eight 16-byte chunks; chunk c of row r sits at
+// c ^ ((r / 2) % 8), so the 16 lanes the LDS serves at once in a fragment read
+// (16 rows at one chunk) touch all 64 banks once.  A load instruction fills
+// eight rows, lane i fetching the chunk that the swizzle puts at its place.
+template <bool UP, bool RAGGED, int MX, int NY, int LDS>
+__device__ __forceinline__ void gemm_tile(const GemmTile &t, const uint16_t *a_src, const int32_t *perm_tok, void *out,
+                                          int d, int d_ff, uint8_t *lds) {
+  constexpr int AB = MX * kBlockB, BB = NY * 4 * kBlockB;  // bytes of an A and of a B slice
+  constexpr int NA = 3, NB = 3 * (AB + BB) <= LDS ? 3 : 2;  // slices in the rings
+  static_assert(NA * AB + NB * BB <= LDS, "the rings fit");
+  constexpr int BN = (UP ? 64 : 128) * NY;           // output features of the tile
+  constexpr int WB = 32 * NY;                        // weight rows of a wave: y 0 and 1 from W1 and W3 in the up projection
+  constexpr int IA = MX, IB = 4 * NY;                // a wave's load instructions per slice
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int K = UP ? d : d_ff, N = UP ? d_ff : d;
+
+  // sources: load instruction i of the wave fills slice rows 8 (4 i + wave) ..
+  // + 7.  Rows past the tile's end read its last row and columns past N the
+  // last one (their results are not written).
+  const int lr = lane / 8, lc = (lane & 7) ^ ((4 * (wave & 1) + lane / 16) & 7);
+  const uint8_t *ap[IA];
+#pragma unroll
+  for (int i = 0; i < IA; ++i) {
+    const int m = t.row + min(8 * (4 * i + wave) + lr, t.rows - 1);
+    ap[i] = reinterpret_cast<const uint8_t *>(a_src + (UP ? (size_t)perm_tok[m] : (size_t)m) * K + 8 * lc);
+  }
+  const int nb = min(BN, N - t.n0);
+  __amdgpu_buffer_rsrc_t brs[UP ? 2 : 1];
+#pragma unroll
+  for (int b = 0; b < (UP ? 2 : 1); ++b)
+    brs[b] = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t *>(t.w + (UP ? (size_t)b * d_ff * d : 2 * (size_t)d_ff * d) + (size_t)t.n0 * K), 0,
+        (uint32_t)nb * K * 2, 0x00020000);
+  uint32_t boff[IB];
+#pragma unroll
+  for (int i = 0; i < IB; ++i) boff[i] = (uint32_t)min((8 * (4 * i + wave) + lr) % BN, nb - 1) * K * 2 + 16 * lc;
+  const uint32_t m0a = (uint32_t)(uintptr_t)(lds_void_t *)lds + wave * (8 * kRowB), m0b = m0a + NA * AB;
+  auto load_a = [&](int i, int s, uint32_t at) {
+    const uint8_t *p = ap[i] + (size_t)s * kRowB;
+    if (RAGGED && s * kKs + 8 * lc >= K) p = reinterpret_cast<const uint8_t *>(g_zeros);
+    dma_rows(p, m0a + at + i * kBlockB);
+  };
+  auto load_b = [&](int i, int s, uint32_t at) {
+    const uint32_t so = (uint32_t)s * kRowB;
+    const __amdgpu_buffer_rsrc_t r = brs[UP ? i / (IB / 2) : 0];
+    if (RAGGED)
+      dma_weights(r, m0b + at + i * kBlockB, s * kKs + 8 * lc >= K ? kOobOffset : boff[i] + so, 0);
+    else
+      dma_weights(r, m0b + at + i * kBlockB, boff[i], so);
+  };
+
+  // fragments: lane i holds row i % 32 of a block, columns 16 h + 8 (i / 32) .. + 7
+  // of part h.  In the up projection a wave's y = 0 rows are of W1 and its
+  // y = 1 rows the same features of W3 (NY = 1: 16 rows of each in one block).
+  const int r32 = lane & 31, hi = lane >> 5, sw = (r32 >> 1) & 7;
+  const uint32_t fa = r32 * kRowB + ((hi ^ sw) << 4);
+  constexpr bool kMixed = UP && NY == 1;
+  const int brow = kMixed ? (r32 < 16 ? 16 * wave + r32 : 64 + 16 * wave + r32 - 16) : (UP ? 32 : WB) * wave + r32;
+  const uint32_t fb = NA * AB + brow * kRowB + ((hi ^ ((brow >> 1) & 7)) << 4);
+  constexpr int YB = (UP ? 128 : 32) * kRowB;
+  struct Frags {
+    bf16x8 a[MX], b[NY];
+  };
+  constexpr int NF = MX + NY;
+  auto rd = [&](Frags &f, int i, uint32_t at_a, uint32_t at_b, int h) {
+    if (i < NY)
+      f.b[i] = frag(lds + ((fb + at_b) ^ (h << 5)) + i * YB);
+    else
+      f.a[i - NY] = frag(lds + ((fa + at_a) ^ (h << 5)) + (i - NY) * kBlockB);
+  };
+
+  floatx16 c[MX][NY];
+#pragma unroll
+  for (int x = 0; x < MX; ++x)
+#pragma unroll
+    for (int y = 0; y < NY; ++y)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) c[x][y][i] = 0.0f;
+
+  const int nk = (K + kKs - 1) / kKs;
+  // fill the rings, oldest slice first, and read the first part
+#pragma unroll
+  for (int s = 0; s < NA; ++s) {
+    if (s < nk) {
+      if (s < NB) {
+#pragma unroll
+        for (int i = 0; i < IB; ++i) load_b(i, s, s * BB);
+      }
+#pragma unroll
+      for (int i = 0; i < IA; ++i) load_a(i, s, s * AB);
+    }
+  }
+  Frags P, Q;
+  if (nk >= NA)
+    wait_vm<IA *(NA - 1) + IB *(NB - 1)>();
+  else
+    wait_vm<0>();
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < NF; ++i) rd(P, i, 0, 0, 0);
+
+  // The products of part F, with the reads of part H into G (two a product)
+  // and COUNT loads spread evenly between them.  The weights are the MFMA's
+  // first operand: a lane's results are then four consecutive features of one
+  // row, one wide store.
+  constexpr int M2 = MX * NY;
+#define MOE_PART(F, G, ATA, ATB, H, COUNT, LOAD)                                                         \
+  _Pragma("unroll") for (int m = 0; m < M2; ++m) {                                                       \
+    _Pragma("unroll") for (int i = 0; i < NF; ++i) if (i / 2 == m || (m == M2 - 1 && i / 2 > m)) rd(G, i, ATA, ATB, H); \
+    c[m / NY][m % NY] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.b[m % NY], F.a[m / NY], c[m / NY][m % NY], 0, 0, 0);  \
+    __builtin_amdgcn_sched_barrier(0);                                                                   \
+    _Pragma("unroll") for (int q = 0; q < (COUNT); ++q)                                                  \
+      if (q * M2 / (COUNT) == m) {                                                                       \
+        LOAD;                                                                                            \
+        __builtin_amdgcn_sched_barrier(0);                                                               \
+      }                                                                                                  \
+  }
+  // Step s multiplies slice s.  Loads of A slice s + 2 go, in its first two
+  // parts, to the place of slice s - 1 (every wave has read it: the barrier of
+  // step s - 1), and loads of B slice s + NB, after the barrier, to the place
+  // of slice s.  At the barrier slice s + 1 has landed: younger than it are A
+  // slices up to s + 2 and B slices up to s + NB - 1.
+  constexpr int A0 = (IA + 1) / 2, A1 = IA - A0;
+  uint32_t at_a = 0, at_b = 0, old_a = 0;
+  for (int s = 0; s < nk; ++s) {
+    const uint32_t next_a = at_a + AB == NA * AB ? 0 : at_a + AB;
+    const uint32_t next_b = at_b + BB == NB * BB ? 0 : at_b + BB;
+    const bool more_a = s > 0 && s + NA - 1 < nk, more_b = s + NB < nk;
+    __builtin_amdgcn_sched_barrier(0);
+    MOE_PART(P, Q, at_a, at_b, 1, A0, if (more_a) load_a(q, s + NA - 1, old_a))
+    MOE_PART(Q, P, at_a, at_b, 2, A1, if (more_a) load_a(A0 + q, s + NA - 1, old_a))
+    MOE_PART(P, Q, at_a, at_b, 3, 0, )
+    if (s + NA - 1 < nk)
+      wait_vm<IA *(NA - 2) + IB *(NB - 2)>();
+    else
+      wait_vm<0>();
+    wait_lds();  // this wave's reads of slice s are done
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    MOE_PART(Q, P, next_a, next_b, 0, IB, if (more_b) load_b(q, s + NB, at_b))  // past the last slice: unused bytes
+    old_a = at_a;
+    at_a = next_a;
+    at_b = next_b;
+  }
+#undef MOE_PART
+
+  // a lane holds row lane % 32 of each block and its features 8 g + 4 (lane / 32) + 0 .. 3
+#pragma unroll
+  for (int x = 0; x < MX; ++x) {
+    if (x * 32 + r32 >= t.rows) continue;
+    const size_t row = (size_t)(t.row + x * 32 + r32) * N;
+    if (UP) {
+      uint16_t *o = static_cast<uint16_t *>(out) + row;
+      constexpr int G = kMixed ? 2 : 4;  // groups of four features a wave's W1 rows make
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        const int n = t.n0 + 8 * G * wave + 8 * g + 4 * hi;
+        if (n < N) {
+          uint32_t v[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            v[i] = bf16_rne(silu(c[x][0][4 * g + i]) * (kMixed ? c[x][0][8 + 4 * g + i] : c[x][NY - 1][4 * g + i]));
+          *reinterpret_cast<u32x2 *>(o + n) = u32x2{v[0] | (v[1] << 16), v[2] | (v[3] << 16)};
+        }
+      }
+    } else {
+      float *o = static_cast<float *>(out) + row;
+#pragma unroll
+      for (int y = 0; y < NY; ++y)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int n = t.n0 + WB * wave + 32 * y + 8 * g + 4 * hi;
+          if (n < N)
+            *reinterpret_cast<floatx4 *>(o + n) =
+                floatx4{c[x][y][4 * g], c[x][y][4 * g + 1], c[x][y][4 * g + 2], c[x][y][4 * g + 3]};
+        }
+    }
+  }
+}
+
+// Workgroup i runs on XCD i % 8; it takes tile (i % 8) * n / 8 + i / 8 (with
+// the remainder spread over the first XCDs), so each XCD works through one
+// contiguous stretch of the tile list and the tiles it runs at the same time
+// share their A and B panels in that XCD's L2.
+__device__ __forceinline__ int xcd_tile(int b, int n) {
+  constexpr int kXcds = 8;
+  const int x = b % kXcds, i = b / kXcds, per = n / kXcds, rem = n % kXcds;
+  return x * per + min(x, rem) + i;
+}
+
+// Wide tiles: up to 256 rows by 256 weight rows, one workgroup a CU.  Narrow
+// ones: up to 64 rows by 128, two workgroups a CU.  list: where the launch's
+// tiles start and how many there are (never more than the grid; the surplus
+// workgroups exit).
+template <bool UP, bool RAGGED, bool WIDE>
+__global__ __launch_bounds__(kThreads, WIDE ? 1 : 2) void prefill_gemm_kernel(const GemmTile *tiles, const int32_t *ntiles,
+                                                                             const uint16_t *a_src, const int32_t *perm_tok,
+                                                                             void *out, int d, int d_ff) {
+  constexpr int LDS = WIDE ? 160 * 1024 : 72 * 1024;
+  __shared__ __align__(1024) uint8_t lds[LDS];
+  const int nt = ntiles ? min(*ntiles, (int)gridDim.x) : (int)gridDim.x;
+  if ((int)blockIdx.x >= nt) return;
+  const GemmTile t = tiles[xcd_tile(blockIdx.x, nt)];
+  if (t.rows <= 0 || t.rows > (WIDE ? kWideRows : kNarrowRows)) return;  // the planners make no such tiles
+#define MOE_CASE(M) \
+  case M: gemm_tile<UP, RAGGED, M, WIDE ? 2 : 1, LDS>(t, a_src, perm_tok, out, d, d_ff, lds); break;
+  if constexpr (WIDE) {
+    switch ((t.rows + 31) / 32) {
+      MOE_CASE(1) MOE_CASE(2) MOE_CASE(3) MOE_CASE(4) MOE_CASE(5) MOE_CASE(6) MOE_CASE(7) MOE_CASE(8)
+    }
+  } else {
+    switch ((t.rows + 31) / 32) { MOE_CASE(1) MOE_CASE(2) }
+  }
+#undef MOE_CASE
+}
+
+template <bool UP>
+hipError_t launch_gemm(const GemmTile *tiles, const int32_t *ntiles, int grid, bool wide, const uint16_t *a_src,
+                       const int32_t *perm_tok, void *out, int d, int d_ff, const Launch &l) {
+  if (grid <= 0) return hipSuccess;
+  const bool ragged = (UP ? d : d_ff) % kKs != 0;
+#define MOE_GEMM(R, W) \
+  MOE_LAUNCH((prefill_gemm_kernel<UP, R, W>), dim3(grid), dim3(kThreads), 0, l, tiles, ntiles, a_src, perm_tok, out, d, d_ff)
+  if (wide) {
+    if (ragged) MOE_GEMM(true, true); else MOE_GEMM(false, true);
+  } else {
+    if (ragged) MOE_GEMM(true, false); else MOE_GEMM(false, false);
+  }
+#undef MOE_GEMM
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_prefill_up(const GemmTile *tiles, const int32_t *ntiles, int grid, bool wide, const uint16_t *xn,
+                             const int32_t *perm_tok, uint16_t *act, int d, int d_ff, const Launch &l) {
+  return launch_gemm<true>(tiles, ntiles, grid, wide, xn, perm_tok, act, d, d_ff, l);
+}
+
+hipError_t launch_prefill_down(const GemmTile *tiles, const int32_t *ntiles, int grid, bool wide, const uint16_t *act,
+                               float *Y, int d, int d_ff, const Launch &l) {
+  return launch_gemm<false>(tiles, ntiles, grid, wide, act, nullptr, Y, d, d_ff, l);
+}
+
+}  // namespace moe
