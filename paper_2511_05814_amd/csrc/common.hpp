@@ -145,17 +145,21 @@ __host__ __device__ inline int tile_rows(int n, int r) {
 }
 
 struct PrefillArgs {
-  const void *gate;  // layer's gate [E][d]
+  const void *gate;  // layer's gate [E][d], bf16
   const float *H;    // [T][d]
   int32_t *ids;      // [T][K]
   float *g;          // [T][K]
-  float *inv_r;      // [T]
   uint16_t *xn;      // [T][d] bf16
-  int T, d, E, K, dtype;
+  double *zpart;     // [splits][T][kMaxE] partial logits of the column ranges
+  uint8_t *blk_cnt;  // [blocks of kRouteTok tokens][kMaxE] tokens that chose the expert
+  uint8_t *blk_last; // and the last pair (token in block * K + rank) that did
+  int T, d, E, K, splits;
 };
+constexpr int kRouteTok = 16;
 
 struct PlanArgs {
   const int32_t *ids;
+  const uint8_t *blk_cnt, *blk_last;  // as in PrefillArgs
   int32_t *perm_tok;  // [T*K] sorted position -> token
   int32_t *pos_of;    // [T*K] (token, rank) -> sorted position
   PrefillPlan *plan;  // [E]
@@ -231,6 +235,8 @@ hipError_t launch_ffnq_up(const FfnArgs &a, const Launch &l);
 hipError_t launch_ffnq_down(const FfnArgs &a, const Launch &l);
 int ffnq_down_chunks(int K, int d_ff);
 hipError_t launch_prefill_gate(const PrefillArgs &a, const Launch &l);
+hipError_t launch_prefill_route(const PrefillArgs &a, const Launch &l);
+int prefill_gate_splits(int T, int d);  // column ranges of a batch's gate launch
 hipError_t launch_prefill_plan(const PlanArgs &a, const Launch &l);
 // Grouped GEMMs over a tile list (wide tiles: up to kWideRows rows by
 // prefill_tile_cols(up, true) output columns; narrow ones up to kNarrowRows by
@@ -283,6 +289,33 @@ __device__ __forceinline__ double wave_sum_d(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
   return v;
+}
+
+// fp64 sum over a wave's lanes, left in lane 63: running sums within rows of
+// 16 lanes (row_shr 1, 2, 4, 8), then row_bcast:15 and row_bcast:31; lanes
+// whose DPP source lies outside the pattern add 0.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_add_d(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROW_MASK, 0xF, false);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_sum_d_to_lane63(double v) {
+  v = dpp_add_d<0x111, 0xF>(v);
+  v = dpp_add_d<0x112, 0xF>(v);
+  v = dpp_add_d<0x114, 0xF>(v);
+  v = dpp_add_d<0x118, 0xF>(v);
+  v = dpp_add_d<0x142, 0xA>(v);
+  v = dpp_add_d<0x143, 0xC>(v);
+  return v;
+}
+
+// Value of x on lane src, for a src the whole wave agrees on (a scalar read,
+// not an LDS round trip like a general shuffle).
+__device__ __forceinline__ int lane_value(int x, int src) { return __builtin_amdgcn_readlane(x, src); }
+__device__ __forceinline__ double lane_value_d(double x, int src) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), src),
+                          __builtin_amdgcn_readlane(__double2loint(x), src));
 }
 
 // Top-K of E <= 64 logits held in LDS, in rank order: larger z first, lower

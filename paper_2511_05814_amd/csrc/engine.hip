@@ -159,7 +159,7 @@ hipError_t scratch_on_device(int dev, uint8_t **out) {
 namespace moe {
 // Prefill workspace for batches of up to T tokens (offsets from its base).
 struct PrefillLayout {
-  size_t ids = 0, g = 0, inv_r = 0, xn = 0, perm = 0, pos = 0, plan = 0, tiles = 0, act = 0,
+  size_t ids = 0, g = 0, zpart = 0, blk_cnt = 0, blk_last = 0, xn = 0, perm = 0, pos = 0, plan = 0, tiles = 0, act = 0,
          y = 0, staging = 0, coded = 0, lists = 0, ntiles = 0, total = 0;
   int tile_cap = 0;  // GEMM tiles the schedule can hold
   int ring = 0;      // staging slots for experts streamed through the batch
@@ -187,7 +187,12 @@ static PrefillLayout prefill_layout(int K, int d, int d_ff, int E, int S, int T,
   p.ring = 2 * half;
   p.ids = take(P * 4);
   p.g = take(P * 4);
-  p.inv_r = take((size_t)T * 4);
+  // a shorter batch takes more column ranges, but never more partial logits
+  // than 512 blocks' worth above the longest batch's
+  const size_t blocks = ((size_t)T + kRouteTok - 1) / kRouteTok;
+  p.zpart = take((blocks + 512) * kRouteTok * kMaxE * sizeof(double));
+  p.blk_cnt = take(blocks * kMaxE);
+  p.blk_last = take(blocks * kMaxE);
   p.xn = take((size_t)T * d * 2);
   p.perm = take(P * 4);
   p.pos = take(P * 4);
@@ -936,7 +941,6 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   uint8_t *base = c->prefill_ws;
   int32_t *ids = reinterpret_cast<int32_t *>(base + p.ids);
   float *g = reinterpret_cast<float *>(base + p.g);
-  float *inv_r = reinterpret_cast<float *>(base + p.inv_r);
   uint16_t *xn = reinterpret_cast<uint16_t *>(base + p.xn);
   int32_t *perm = reinterpret_cast<int32_t *>(base + p.perm);
   int32_t *pos = reinterpret_cast<int32_t *>(base + p.pos);
@@ -947,25 +951,29 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   uint8_t *staging = base + p.staging;
   const uint8_t *host = c->host_layer[layer];
   uint8_t *arena = static_cast<uint8_t *>(c->desc.arena);
-  const int gate_elem = c->dtype == MOE_DTYPE_BF16 ? 2 : 4;
 
   hipEvent_t tp;
   HIP_TRY(c, span_begin(c, c->cs, &tp, SPAN_PREFILL));
   PrefillArgs ga{};
-  ga.gate = static_cast<const uint8_t *>(c->desc.gate_w) + (size_t)layer * c->E * c->d * gate_elem;
+  ga.gate = static_cast<const uint8_t *>(c->desc.gate_w) + (size_t)layer * c->E * c->d * 2;  // bf16
   ga.H = H;
   ga.ids = ids;
   ga.g = g;
-  ga.inv_r = inv_r;
+  ga.zpart = reinterpret_cast<double *>(base + p.zpart);
+  ga.blk_cnt = base + p.blk_cnt;
+  ga.blk_last = base + p.blk_last;
   ga.xn = xn;
   ga.T = T;
   ga.d = c->d;
   ga.E = c->E;
   ga.K = c->K;
-  ga.dtype = c->dtype;
+  ga.splits = prefill_gate_splits(T, c->d);
   HIP_TRY(c, launch_prefill_gate(ga, Launch{c->cs}));
+  HIP_TRY(c, launch_prefill_route(ga, Launch{c->cs}));
   PlanArgs pa{};
   pa.ids = ids;
+  pa.blk_cnt = ga.blk_cnt;
+  pa.blk_last = ga.blk_last;
   pa.perm_tok = perm;
   pa.pos_of = pos;
   pa.plan = plan;

@@ -30,6 +30,7 @@
 #include "common.hpp"
 #include "moe_offload.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace moe {
@@ -40,7 +41,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef double double4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kGateTok = 16;     // tokens per gate workgroup
+constexpr int kGateTok = kRouteTok;  // tokens per gate and route workgroup
 
 __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   uint32_t u = __float_as_uint(f);
@@ -59,238 +60,203 @@ __device__ __forceinline__ float silu(float v) { return v / (1.0f + __expf(-v));
 // experts; lane l supplies A[l % 16][l / 16] and B[l / 16][l % 16] and gets
 // back D[l / 16 + 4 v][l % 16], v = 0..3.
 //
-// A workgroup holds 16 tokens and all experts.  The columns are cut into
-// 16-wide blocks dealt round-robin to the eight waves (two a SIMD, so one
-// wave's loads and conversions overlap the other's products), so each wave
-// reads a distinct eighth of H.  In a block, lane (i, kq) = (lane % 16, lane / 16)
-// loads columns 4kq .. 4kq+3 of token row i and of expert row 16g + i for
-// each expert group g, and MFMA step s uses column 4kq + s of both, so A and
-// B always pair the same column.  The waves' partial sums meet in LDS and
-// are added in wave order.
-// At 4096 tokens, d 2048, 64 experts: four waves with eight blocks ahead
-// 54.6 us, eight waves with two ahead 40.3 (four ahead: 43.3), sixteen with
-// one 40.6.
+// A workgroup takes 16 tokens and one of `splits` ranges of columns, so that
+// small batches still fill the chip, and leaves its partial logits in memory;
+// the route kernel adds the ranges in order.  Its eight waves are the groups
+// of 16 experts times cw shares of the columns: lane (i, kq) = (lane % 16,
+// lane / 16) of a wave loads columns 8 kq .. + 7 of token row i and of expert
+// row 16 g + i of each 32-column block, and MFMA step s uses column 8 kq + s
+// of both, so A and B always pair the same column.  The column shares of a
+// group meet in LDS and are added in order.
+//
+// Bound by latency below some 500 tokens and by the fp64 matrix rate (13.7 us
+// at 4096 tokens) above.  d 2048, 64 experts, us in the trace, one kernel of a
+// workgroup per 16 tokens before / gate + route now: 32 tokens 35.8 / 5.3 +
+// 11.6, 509 tokens 37 / 9.3 + 12.1, 4096 tokens 40-47 / 29-39 + 12-16.  A whole
+// batch with d_ff 64 (plan and GEMMs included): 86, 131, 282 before, 51, 73,
+// 233 now.
 constexpr int kGateWaves = 8;
 constexpr int kGateThreads = kGateWaves * kWave;
-constexpr int kGateAhead = 2;  // blocks in flight per wave
+constexpr int kGateAhead = 4;      // 32-column blocks in flight per wave
+constexpr int kGateCols = 32;      // columns of a block
 
 struct GateBlock {
-  float4 h;              // 4 columns of this lane's token row
-  uint2 w[kMaxE / 16];   // 4 bf16 columns of this lane's row in each expert group
-  float4 wf[kMaxE / 16]; // fp32 gate weights instead (dtype 0)
+  float4 h[2];  // 8 columns of this lane's token row
+  uint4 w;      // 8 bf16 columns of its expert row
 };
 
-// FAST (d a multiple of 16 * kGateWaves * kGateAhead): every block the loop
-// multiplies lies inside d, so loads are unconditional; the look-ahead past
-// the end reads the row's last columns and is never used, and rows past T or
-// experts past E (clamped to the last valid one) only feed logits nobody reads.
-// A guarded load would be waited for on the spot.
-template <int DT, bool FAST>
-__device__ __forceinline__ void gate_load(GateBlock &b, const float *hrow, const uint8_t *wbase, int ng, int k,
-                                          int d, int E, int i) {
-  if (FAST) {
-    const int kk = min(k, d - 4);
-    b.h = *reinterpret_cast<const float4 *>(hrow + kk);
-#pragma unroll
-    for (int g = 0; g < kMaxE / 16; ++g) {
-      if (g >= ng) break;
-      const int e = min(16 * g + i, E - 1);
-      if (DT == 1)
-        b.w[g] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(wbase) + (size_t)e * d + kk);
-      else
-        b.wf[g] = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(wbase) + (size_t)e * d + kk);
-    }
-    return;
-  }
-  b.h = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (hrow && k < d) b.h = *reinterpret_cast<const float4 *>(hrow + k);
-#pragma unroll
-  for (int g = 0; g < kMaxE / 16; ++g) {
-    const int e = 16 * g + i;
-    if (DT == 1) {
-      b.w[g] = make_uint2(0, 0);
-      if (g < ng && e < E && k < d)
-        b.w[g] = *reinterpret_cast<const uint2 *>(reinterpret_cast<const uint16_t *>(wbase) + (size_t)e * d + k);
-    } else {
-      b.wf[g] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (g < ng && e < E && k < d)
-        b.wf[g] = *reinterpret_cast<const float4 *>(reinterpret_cast<const float *>(wbase) + (size_t)e * d + k);
-    }
-  }
-}
-
-template <int DT>
-__device__ __forceinline__ void gate_mfma(const GateBlock &b, int ng, double4_t *acc, double &sq) {
-  const double h4[4] = {b.h.x, b.h.y, b.h.z, b.h.w};
-#pragma unroll
-  for (int s = 0; s < 4; ++s) sq = fma(h4[s], h4[s], sq);
-#pragma unroll
-  for (int g = 0; g < kMaxE / 16; ++g) {
-    if (g >= ng) break;
-    double w4[4];
-    if (DT == 1) {
-      w4[0] = __uint_as_float(b.w[g].x << 16);
-      w4[1] = __uint_as_float(b.w[g].x & 0xFFFF0000u);
-      w4[2] = __uint_as_float(b.w[g].y << 16);
-      w4[3] = __uint_as_float(b.w[g].y & 0xFFFF0000u);
-    } else {
-      w4[0] = b.wf[g].x;
-      w4[1] = b.wf[g].y;
-      w4[2] = b.wf[g].z;
-      w4[3] = b.wf[g].w;
-    }
-#pragma unroll
-    for (int s = 0; s < 4; ++s) acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(h4[s], w4[s], acc[g], 0, 0, 0);
-  }
-}
-
-template <int DT, bool FAST>
-__device__ __forceinline__ void gate_partial(const PrefillArgs &a, int t0, int wave, int lane,
-                                             double (*zp)[kGateTok][kMaxE], double (*rp)[kGateTok]) {
+// (batches run on bf16 models only, so the gate is bf16)
+template <bool RAGGED>
+__global__ __launch_bounds__(kGateThreads) void prefill_gate_kernel(PrefillArgs a) {
+  __shared__ double zp[kGateWaves][kGateTok][16];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int d = a.d, E = a.E;
   const int i = lane % 16, kq = lane / 16;
-  const int ng = (E + 15) / 16;
-  const float *hrow = FAST ? a.H + (size_t)min(t0 + i, a.T - 1) * d
-                           : (t0 + i < a.T ? a.H + (size_t)(t0 + i) * d : nullptr);
-  const uint8_t *wbase = static_cast<const uint8_t *>(a.gate);
-  double4_t acc[kMaxE / 16];
+  const int t0 = blockIdx.x * kGateTok, split = blockIdx.y;
+  const int ng = (E + 15) / 16, cw = kGateWaves / ng;  // expert groups, column shares
+  const int g = wave % ng, cs = wave / ng;
+  // blocks of this range, dealt round-robin to the column shares
+  const int nb = (d + kGateCols - 1) / kGateCols;
+  const int b0 = nb * split / a.splits, b1 = nb * (split + 1) / a.splits;
+  const bool live = cs < cw;
+  double4_t acc[2] = {};
+  if (live) {
+    // rows past T and experts past E read the last valid one: logits nobody reads
+    const float *hrow = a.H + (size_t)min(t0 + i, a.T - 1) * d;
+    const uint8_t *wrow = static_cast<const uint8_t *>(a.gate) + (size_t)min(16 * g + i, E - 1) * d * 2;
+    GateBlock buf[kGateAhead];
+    auto load = [&](GateBlock &b, int blk) {
+      // unconditional (past the range: its last block again, unused); a
+      // ragged d reads its last 8 columns instead of columns past the end
+      const int k = min(min(blk, b1 - 1) * kGateCols + 8 * kq, RAGGED ? d - 8 : d);
+      b.h[0] = *reinterpret_cast<const float4 *>(hrow + k);
+      b.h[1] = *reinterpret_cast<const float4 *>(hrow + k + 4);
+      b.w = *reinterpret_cast<const uint4 *>(wrow + (size_t)k * 2);
+    };
+    auto mul = [&](const GateBlock &b, int blk) {
+      const bool in = !RAGGED || blk * kGateCols + 8 * kq < d;
+      float h[8] = {b.h[0].x, b.h[0].y, b.h[0].z, b.h[0].w, b.h[1].x, b.h[1].y, b.h[1].z, b.h[1].w}, w[8];
+      bf16x8_to_f32(b.w, w);
 #pragma unroll
-  for (int g = 0; g < kMaxE / 16; ++g) acc[g] = double4_t{0.0, 0.0, 0.0, 0.0};
-  double sq = 0.0;
-  const int stride = 16 * kGateWaves;
-  GateBlock buf[kGateAhead];
+      for (int s = 0; s < 8; ++s)
+        acc[s & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? (double)h[s] : 0.0, in ? (double)w[s] : 0.0, acc[s & 1], 0, 0, 0);
+    };
+    // this wave's blocks: first, first + cw, ...; straight-line main loop, the
+    // last blocks, which load nothing, peeled off
+    const int first = b0 + cs, n = first < b1 ? (b1 - first + cw - 1) / cw : 0;
 #pragma unroll
-  for (int j = 0; j < kGateAhead; ++j) gate_load<DT, FAST>(buf[j], hrow, wbase, ng, (wave + j * kGateWaves) * 16 + 4 * kq, d, E, i);
-  for (int k0 = wave * 16; k0 < d; k0 += stride * kGateAhead) {
+    for (int u = 0; u < kGateAhead; ++u) load(buf[u], first + u * cw);
+    int j = 0;
+    for (; j + kGateAhead < n; j += kGateAhead) {
 #pragma unroll
-    for (int j = 0; j < kGateAhead; ++j) {
-      const GateBlock cur = buf[j];
-      gate_load<DT, FAST>(buf[j], hrow, wbase, ng, k0 + (j + kGateAhead) * stride + 4 * kq, d, E, i);
-      gate_mfma<DT>(cur, ng, acc, sq);
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < kMaxE / 16; ++g)
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-      if (16 * g + i < E) zp[wave][kq + 4 * v][16 * g + i] = acc[g][v];
-  sq += __shfl_xor(sq, 16, kWave);
-  sq += __shfl_xor(sq, 32, kWave);
-  if (kq == 0) rp[wave][i] = sq;
-}
-
-__global__ __launch_bounds__(kGateThreads) void prefill_gate_kernel(PrefillArgs a) {
-  __shared__ double zp[kGateWaves][kGateTok][kMaxE];
-  __shared__ double rp[kGateWaves][kGateTok];
-  __shared__ int s_top[kGateWaves][kMaxK];
-  __shared__ float s_inv[kGateTok];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int t0 = blockIdx.x * kGateTok;
-  const int E = a.E, d = a.d;
-  const bool fast = d % (16 * kGateWaves * kGateAhead) == 0;
-  if (a.dtype == 1) {
-    if (fast)
-      gate_partial<1, true>(a, t0, wave, lane, zp, rp);
-    else
-      gate_partial<1, false>(a, t0, wave, lane, zp, rp);
-  } else {
-    if (fast)
-      gate_partial<0, true>(a, t0, wave, lane, zp, rp);
-    else
-      gate_partial<0, false>(a, t0, wave, lane, zp, rp);
-  }
-  __syncthreads();
-  // zs = zp[0] + zp[1] + ... in wave order, kept in zp[0]
-  for (int x = tid; x < kGateTok * kMaxE; x += kGateThreads) {
-    const int r = x / kMaxE, e = x % kMaxE;
-    if (e < E) {
-      double z = zp[0][r][e];
-#pragma unroll
-      for (int w = 1; w < kGateWaves; ++w) z += zp[w][r][e];
-      zp[0][r][e] = z;
-    }
-  }
-  if (tid < kGateTok) {
-    double r = rp[0][tid];
-#pragma unroll
-    for (int w = 1; w < kGateWaves; ++w) r += rp[w][tid];
-    rp[0][tid] = r;
-    const float inv = (float)(1.0 / sqrt(r / (double)d + 1e-5));
-    s_inv[tid] = inv;
-    if (t0 + tid < a.T) a.inv_r[t0 + tid] = inv;
-  }
-  __syncthreads();
-  double (*zs)[kMaxE] = zp[0];
-  double *rs = rp[0];
-
-  // top-K per token: wave w handles tokens TW w .. TW w + TW - 1
-  constexpr int TW = kGateTok / kGateWaves;
-  static_assert(kGateTok % kGateWaves == 0, "whole tokens per wave");
-  for (int q = 0; q < TW; ++q) {
-    const int r = wave * TW + q;
-    const int t = t0 + r;
-    if (t >= a.T) break;
-    const int mine = wave_topk_lds(zs[r], E, a.K, lane, s_top[wave]);
-    const double rr = sqrt(rs[r] / (double)d + 1e-5);
-    const double zr = (lane < a.K) ? zs[r][mine] : 0.0;
-    const double z0 = __shfl(zr, 0, kWave);
-    const double ex = (lane < a.K) ? exp((zr - z0) / rr) : 0.0;
-    double den = ex;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) den += __shfl_xor(den, o, kWave);
-    if (lane < a.K) {
-      a.ids[(size_t)t * a.K + lane] = mine;
-      a.g[(size_t)t * a.K + lane] = (float)(ex / den);
-    }
-  }
-  // normalised bf16 rows of all the workgroup's tokens, every thread taking
-  // part, eight loads in flight (clamped, so none waits behind a branch); a
-  // wave starts on them as soon as its tokens' top-K is written (1/r was set
-  // with the sums)
-  constexpr int kRowAhead = 8;
-  const int nt = min(kGateTok, a.T - t0);
-  const int q4 = d / 4;  // float4 per row
-  const int total = nt * q4;
-  for (int i0 = tid; i0 < total; i0 += kRowAhead * kGateThreads) {
-    float4 v[kRowAhead];
-#pragma unroll
-    for (int u = 0; u < kRowAhead; ++u) {
-      const int i = min(i0 + u * kGateThreads, total - 1);
-      const int r = i / q4, c = (i - r * q4) * 4;
-      v[u] = *reinterpret_cast<const float4 *>(a.H + (size_t)(t0 + r) * d + c);
-    }
-#pragma unroll
-    for (int u = 0; u < kRowAhead; ++u) {
-      const int i = i0 + u * kGateThreads;
-      if (i < total) {
-        const int r = i / q4, c = (i - r * q4) * 4;
-        const float inv = s_inv[r];
-        uint2 o;
-        o.x = (uint32_t)f32_to_bf16_rne(v[u].x * inv) | ((uint32_t)f32_to_bf16_rne(v[u].y * inv) << 16);
-        o.y = (uint32_t)f32_to_bf16_rne(v[u].z * inv) | ((uint32_t)f32_to_bf16_rne(v[u].w * inv) << 16);
-        *reinterpret_cast<uint2 *>(a.xn + (size_t)(t0 + r) * d + c) = o;
+      for (int u = 0; u < kGateAhead; ++u) {
+        mul(buf[u], first + (j + u) * cw);
+        load(buf[u], first + (j + u + kGateAhead) * cw);
+        __builtin_amdgcn_sched_barrier(0);  // keep each refill next to its block
       }
     }
+#pragma unroll
+    for (int u = 0; u < kGateAhead; ++u)
+      if (j + u < n) mul(buf[u], first + (j + u) * cw);
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) zp[wave][kq + 4 * v][i] = acc[0][v] + acc[1][v];
+  __syncthreads();
+  for (int x = tid; x < kGateTok * kMaxE; x += kGateThreads) {
+    const int r = x / kMaxE, e = x % kMaxE;
+    if (e < E && t0 + r < a.T) {
+      double z = zp[e / 16][r][e % 16];
+      for (int c = 1; c < cw; ++c) z += zp[c * ng + e / 16][r][e % 16];
+      a.zpart[((size_t)split * a.T + t0 + r) * kMaxE + e] = z;
+    }
+  }
+}
+
+// One wave per token: the partial logits added in order, rms in fp64, top-K by
+// rank counting, renormalised softmax weights and the normalised bf16 row; a
+// workgroup's 16 tokens also leave how many of them chose each expert and the
+// last (token, rank) pair that did, from which the plan kernel's workgroups
+// find their places without passing over all pairs.  The row's loads are
+// issued first and stay in registers up to 256 * NV columns.
+template <int NV>
+__global__ __launch_bounds__(kGateTok *kWave) void prefill_route_kernel(PrefillArgs a) {
+  __shared__ double zs[kGateTok][kMaxE];
+  __shared__ int s_top[kGateTok][kMaxK];
+  __shared__ int s_cnt[kMaxE], s_last[kMaxE];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int d = a.d, E = a.E, K = a.K;
+  const int t = blockIdx.x * kGateTok + wave;
+  if (tid < kMaxE) {
+    s_cnt[tid] = 0;
+    s_last[tid] = 0;
+  }
+  __syncthreads();
+  if (t < a.T) {  // the same for the whole wave
+    const float *row = a.H + (size_t)t * d;
+    float4 v[NV];
+#pragma unroll
+    for (int u = 0; u < NV; ++u) v[u] = *reinterpret_cast<const float4 *>(row + min(u * 256 + lane * 4, d - 4));
+    const double *zr0 = a.zpart + (size_t)t * kMaxE + min(lane, E - 1);
+    const size_t zstride = (size_t)a.T * kMaxE;
+    constexpr int kAhead = 8;  // partial logits in flight (clamped past the last, unused)
+    double zv[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) zv[u] = zr0[min(u, a.splits - 1) * zstride];
+    double z = zv[0];
+    for (int s0 = 0; s0 < a.splits; s0 += kAhead) {
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) {
+        if (s0 + u > 0) z += s0 + u < a.splits ? zv[u] : 0.0;
+        zv[u] = zr0[min(s0 + u + kAhead, a.splits - 1) * zstride];
+      }
+    }
+    zs[wave][lane] = z;
+    double sq = 0.0;
+    auto square = [&](const float4 &q) {
+      sq = fma((double)q.x, (double)q.x, sq);
+      sq = fma((double)q.y, (double)q.y, sq);
+      sq = fma((double)q.z, (double)q.z, sq);
+      sq = fma((double)q.w, (double)q.w, sq);
+    };
+#pragma unroll
+    for (int u = 0; u < NV; ++u)
+      if (u * 256 + lane * 4 < d) square(v[u]);
+    for (int c = NV * 256 + lane * 4; c < d; c += 256) square(*reinterpret_cast<const float4 *>(row + c));
+    const double rr = sqrt(lane_value_d(wave_sum_d_to_lane63(sq), kWave - 1) / (double)d + 1e-5);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int mine = wave_topk_lds(zs[wave], E, K, lane, s_top[wave]);
+    const double zr = lane < K ? zs[wave][mine] : 0.0;
+    const double z0 = lane_value_d(zr, 0);
+    const double ex = lane < K ? exp((zr - z0) / rr) : 0.0;
+    const double den = lane_value_d(wave_sum_d_to_lane63(ex), kWave - 1);
+    if (lane < K) {
+      a.ids[(size_t)t * K + lane] = mine;
+      a.g[(size_t)t * K + lane] = (float)(ex / den);
+      atomicAdd(&s_cnt[mine], 1);
+      atomicMax(&s_last[mine], wave * K + lane);
+    }
+    const float inv = (float)(1.0 / rr);
+    uint16_t *xr = a.xn + (size_t)t * d;
+    auto put = [&](const float4 &q, int c) {
+      uint2 o;
+      o.x = (uint32_t)f32_to_bf16_rne(q.x * inv) | ((uint32_t)f32_to_bf16_rne(q.y * inv) << 16);
+      o.y = (uint32_t)f32_to_bf16_rne(q.z * inv) | ((uint32_t)f32_to_bf16_rne(q.w * inv) << 16);
+      *reinterpret_cast<uint2 *>(xr + c) = o;
+    };
+#pragma unroll
+    for (int u = 0; u < NV; ++u)
+      if (u * 256 + lane * 4 < d) put(v[u], u * 256 + lane * 4);
+    for (int c = NV * 256 + lane * 4; c < d; c += 256) put(*reinterpret_cast<const float4 *>(row + c), c);
+  }
+  __syncthreads();
+  if (tid < kMaxE) {
+    a.blk_cnt[(size_t)blockIdx.x * kMaxE + tid] = (uint8_t)s_cnt[tid];   // at most 16: a token names an expert once
+    a.blk_last[(size_t)blockIdx.x * kMaxE + tid] = (uint8_t)s_last[tid];  // below 16 * 16
   }
 }
 
 // ---------------------------------------------------------------------------
 // 2. sort by expert and update the layer's table for the whole batch
 //
-// A counting sort in one workgroup: count the pairs of each expert (LDS
-// atomics that return nothing), take offsets, then give each pair the next
-// position of its expert (atomics that return it).  Positions within an
-// expert follow the atomics' order, which varies from run to run; nothing
-// downstream depends on it, since every row of the grouped GEMMs is computed
-// alone and the combine reads each (token, rank) pair through pos_of.  Each
-// thread loads kPlanAhead ids before using the first.  (Placing each pair
-// after the earlier pairs of its expert, with one wave's lanes of an expert
-// found by ballots so no two lanes met on one counter, took 39 us against
-// 22 us for these two passes at 4096 tokens of top-8 over 64 experts.)
+// A counting sort over the route kernel's per-block counts.  Every workgroup
+// adds up all of them (64 bytes a block of 16 tokens), which gives it the
+// experts' totals and how many pairs of each lie before its own blocks, and
+// then places its own pairs (LDS atomics that return the position).  Positions
+// within a workgroup's share follow the atomics' order, which varies from run
+// to run; nothing downstream depends on it, since every row of the grouped
+// GEMMs is computed alone and the combine reads each (token, rank) pair
+// through pos_of.  Workgroup 0 also updates the table.  32768 pairs of 64
+// experts: 26-32 us by one workgroup passing twice
+// over the pairs, 12-15 so.
 constexpr int kPlanThreads = 1024;
-constexpr int kPlanAhead = 8;
+constexpr int kPlanWaves = kPlanThreads / kWave;
+constexpr int kPlanAhead = 8;  // blocks' counts in flight per wave
 
 __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) {
+  __shared__ int part[3][kPlanWaves][kMaxE];  // totals, totals before this share, last pair + 1
   __shared__ int cnt[kMaxE], cur[kMaxE], lastp[kMaxE], offs[kMaxE];
   // tile lists (when a.ntiles): cost of each row-block size, the expert's
   // first tile and rows per tile in each list, the lists' lengths
@@ -300,114 +266,139 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
   __shared__ int bad;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int E = a.E, P = a.T * a.K;
-  if (tid < kMaxE) {
-    cnt[tid] = 0;
-    cur[tid] = 0;
-    lastp[tid] = 0;
+  const int nblk = (a.T + kGateTok - 1) / kGateTok;
+  const int b0 = (int)((long)nblk * blockIdx.x / gridDim.x), b1 = (int)((long)nblk * (blockIdx.x + 1) / gridDim.x);
+  // everything that depends on nothing is loaded first: the table (workgroup
+  // 0's first wave), the first of this share's ids and the blocks' counts
+  LayerTable *T = a.table;
+  const bool in_range = lane < E;
+  const bool keeper = wave == 0 && blockIdx.x == 0;  // the wave that updates the table
+  const int le = min(lane, E - 1);
+  int slot0 = T->expert_slot[le];
+  uint32_t count = 0;
+  int64_t last = 0, clock0 = 0, token0 = 0;
+  int pf = 0;
+  uint64_t tbase = 0;
+  if (keeper) {
+    count = T->count[le];
+    last = T->last[le];
+    pf = T->pf[le];
+    clock0 = T->clock;
+    token0 = T->lookups;
+    tbase = *a.trace_in;
   }
+  const int p_lo = b0 * kGateTok * a.K, p_hi = min(P, b1 * kGateTok * a.K);
+  const int id0 = p_lo < p_hi ? a.ids[min(p_lo + tid, p_hi - 1)] : 0;
   if (tid == 0) bad = 0;
-  __syncthreads();
-  if (a.tiles && tid < E) {
-    // every expert has a slot from the warm start on, so its slot is the same
-    // before and after the batch; no tile is ever made without one
-    const int slot = a.table->expert_slot[tid];
-    tw[tid] = slot >= 0 && slot < a.S ? reinterpret_cast<const uint16_t *>(a.arena_layer + (size_t)slot * a.slot_bytes) : nullptr;
-    if (!tw[tid]) bad = 1;
-    // an invalid batch leaves empty tiles
-    if (!a.ntiles) a.tiles[tid] = GemmTile{nullptr, 0, 0, 0, 0};
-    if (a.ntiles && tid < 2) a.ntiles[tid] = 0;
-  }
-  __syncthreads();
-  for (int p0 = tid; p0 < P; p0 += kPlanAhead * kPlanThreads) {
-    int ev[kPlanAhead];
+  int tot = 0, before = 0, lp = 0;
+  for (int b = wave; b < nblk; b += kPlanAhead * kPlanWaves) {
+    int c[kPlanAhead], l[kPlanAhead];
 #pragma unroll
     for (int u = 0; u < kPlanAhead; ++u) {
-      const int p = p0 + u * kPlanThreads;
-      ev[u] = p < P ? a.ids[p] : 0;
+      const size_t at = (size_t)min(b + u * kPlanWaves, nblk - 1) * kMaxE + lane;
+      c[u] = a.blk_cnt[at];
+      l[u] = blockIdx.x == 0 ? a.blk_last[at] : 0;  // only the table needs it
     }
 #pragma unroll
     for (int u = 0; u < kPlanAhead; ++u) {
-      const int p = p0 + u * kPlanThreads;
-      if (p < P) {
-        if (ev[u] < 0 || ev[u] >= E) {
-          bad = 1;
-        } else {
-          atomicAdd(&cnt[ev[u]], 1);
-          atomicMax(&lastp[ev[u]], p + 1);
-        }
-      }
+      const int bu = b + u * kPlanWaves;
+      const int n = bu < nblk ? c[u] : 0;
+      tot += n;
+      before += bu < b0 ? n : 0;
+      lp = n > 0 ? max(lp, bu * kGateTok * a.K + l[u] + 1) : lp;
     }
   }
-  __syncthreads();
-  if (bad) {
-    if (tid == 0) {
-      *a.err = ERR_BAD_LIST;
-      *a.trace_out = *a.trace_in;
-    }
-    return;
-  }
-  if (a.ntiles && wave < kWideRows / 32) {
-    // wave w: what the lists cost with row blocks of at most 32 (w + 1) rows
-    const int n = lane < E ? cnt[lane] : 0;
-    const int per = n > 0 ? tile_rows(n, 32 * (wave + 1)) : 32;
-    int nt = (n + per - 1) / per, blocks = nt * (per / 32);
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      nt += __shfl_xor(nt, o, kWave);
-      blocks += __shfl_xor(blocks, o, kWave);
-    }
-    if (lane < 2) {
-      const TileList &tl = lane == 0 ? a.up : a.dn;
-      const int r = 32 * (wave + 1);
-      tcost[lane][wave] = r >= tl.lo && r <= tl.hi ? tile_cost(tl.cb * nt, tl.cb * blocks, a.cus) : __builtin_inff();
-    }
-  }
+  part[0][wave][lane] = tot;
+  part[1][wave][lane] = before;
+  part[2][wave][lane] = lp;
   __syncthreads();
   if (wave == 0) {
-    const int c = lane < E ? cnt[lane] : 0;
-    int incl = c;
+    int n = 0, bf = 0, l = 0;
+#pragma unroll
+    for (int w = 0; w < kPlanWaves; ++w) {
+      n += part[0][w][lane];
+      bf += part[1][w][lane];
+      l = max(l, part[2][w][lane]);
+    }
+    int incl = n;
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
       const int v = __shfl_up(incl, o, kWave);
       if (lane >= o) incl += v;
     }
-    if (lane < E) offs[lane] = incl - c;
-    if (a.ntiles) {
-      // expert e's tiles: nt row blocks in each column block; the lists' first
-      // tile of each expert by the same scan
+    cnt[lane] = n;
+    lastp[lane] = l;
+    offs[lane] = incl - n;
+    cur[lane] = incl - n + bf;
+    if (a.tiles) {
+      // every expert has a slot from the warm start on, so its slot is the
+      // same before and after the batch; no tile is ever made without one
+      const bool ok = !in_range || (slot0 >= 0 && slot0 < a.S);
+      tw[lane] = in_range && ok ? reinterpret_cast<const uint16_t *>(a.arena_layer + (size_t)slot0 * a.slot_bytes) : nullptr;
+      if (!ok) bad = 1;
+    }
+  }
+  __syncthreads();
+  // place this share's pairs
+  for (int p = p_lo + tid; p < p_hi; p += kPlanThreads) {
+    const int e = p == p_lo + tid ? id0 : a.ids[p];
+    if (e < 0 || e >= E) {  // cannot happen: the route kernel ranks experts 0 .. E - 1
+      *a.err = ERR_BAD_LIST;
+      continue;
+    }
+    const int pos = atomicAdd(&cur[e], 1);
+    a.perm_tok[pos] = p / a.K;
+    a.pos_of[p] = pos;
+  }
+  if (a.ntiles) {
+    if (wave >= 1 && wave <= kWideRows / 32) {
+      // wave w: what the lists cost with row blocks of at most 32 w rows
+      const int n = in_range ? cnt[lane] : 0;
+      const int per = n > 0 ? tile_rows(n, 32 * wave) : 32;
+      int nt = (n + per - 1) / per, blocks = nt * (per / 32);
 #pragma unroll
-      for (int li = 0; li < 2; ++li) {
-        const TileList &tl = li == 0 ? a.up : a.dn;
-        int best = kWideRows / 32 - 1;
-        for (int w = kWideRows / 32 - 2; w >= 0; --w) best = tcost[li][w] < tcost[li][best] ? w : best;
-        const int per = c > 0 ? tile_rows(c, 32 * (best + 1)) : 32;
-        const int mine = (c + per - 1) / per * tl.cb;
-        int it = mine;
+      for (int o = 32; o > 0; o >>= 1) {
+        nt += __shfl_xor(nt, o, kWave);
+        blocks += __shfl_xor(blocks, o, kWave);
+      }
+      if (lane < 2) {
+        const TileList &tl = lane == 0 ? a.up : a.dn;
+        const int r = 32 * wave;
+        tcost[lane][wave - 1] = r >= tl.lo && r <= tl.hi ? tile_cost(tl.cb * nt, tl.cb * blocks, a.cus) : __builtin_inff();
+      }
+    }
+    __syncthreads();
+    if (wave < 2) {
+      // wave li: expert e's tiles of list li, nt row blocks in each column
+      // block, and the list's first tile of each expert
+      const int li = wave;
+      const TileList &tl = li == 0 ? a.up : a.dn;
+      const int c = in_range ? cnt[lane] : 0;
+      int best = kWideRows / 32 - 1;
+      for (int w = kWideRows / 32 - 2; w >= 0; --w) best = tcost[li][w] < tcost[li][best] ? w : best;
+      const int per = c > 0 ? tile_rows(c, 32 * (best + 1)) : 32;
+      const int mine = (c + per - 1) / per * tl.cb;
+      int it = mine;
 #pragma unroll
-        for (int o = 1; o < kWave; o <<= 1) {
-          const int v = __shfl_up(it, o, kWave);
-          if (lane >= o) it += v;
-        }
-        if (lane < E) {
-          trows[li][lane] = per;
-          tfirst[li][lane] = it - mine;
-        }
-        if (lane == kWave - 1) {
-          const bool fits = it <= tl.cap;  // the host's bound holds for any counts
-          tlen[li] = fits ? it : 0;
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int v = __shfl_up(it, o, kWave);
+        if (lane >= o) it += v;
+      }
+      trows[li][lane] = per;
+      tfirst[li][lane] = it - mine;
+      if (lane == kWave - 1) {
+        const bool fits = it <= tl.cap && !bad;  // the host's bound holds for any counts
+        tlen[li] = fits ? it : 0;
+        if (blockIdx.x == 0) {
           a.ntiles[li] = tlen[li];
           if (!fits) *a.err = ERR_BAD_LIST;
         }
       }
-    } else if (a.tiles && lane < E) {
-      a.tiles[lane] = GemmTile{tw[lane], incl - c, c, 0, 0};
     }
-  }
-  __syncthreads();
-  if (a.ntiles) {
+    __syncthreads();
     // tile i of a list belongs to the last expert whose first tile is <= i
     const int nup = tlen[0], n_all = tlen[0] + tlen[1];
-    for (int i = tid; i < n_all; i += kPlanThreads) {
+    for (int i = blockIdx.x * kPlanThreads + tid; i < n_all; i += gridDim.x * kPlanThreads) {
       const int list = i < nup ? 0 : 1;
       const int li = list == 0 ? i : i - nup;
       int lo = 0, hi = E - 1;
@@ -424,36 +415,19 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
       a.tiles[(list == 0 ? a.up.first : a.dn.first) + li] =
           GemmTile{tw[lo], offs[lo] + mb * per, min(per, cnt[lo] - mb * per), cb * (list == 0 ? a.up.cols : a.dn.cols), 0};
     }
+  } else if (a.tiles && keeper && in_range) {
+    a.tiles[lane] = GemmTile{tw[lane], offs[lane], bad ? 0 : cnt[lane], 0, 0};
+    if (bad) *a.err = ERR_BAD_LIST;
   }
-  for (int p0 = tid; p0 < P; p0 += kPlanAhead * kPlanThreads) {
-    int ev[kPlanAhead];
-#pragma unroll
-    for (int u = 0; u < kPlanAhead; ++u) {
-      const int p = p0 + u * kPlanThreads;
-      ev[u] = p < P ? a.ids[p] : 0;
-    }
-#pragma unroll
-    for (int u = 0; u < kPlanAhead; ++u) {
-      const int p = p0 + u * kPlanThreads;
-      if (p < P) {
-        const int pos = offs[ev[u]] + atomicAdd(&cur[ev[u]], 1);
-        a.perm_tok[pos] = p / a.K;
-        a.pos_of[p] = pos;
-      }
-    }
-  }
-  if (wave != 0) return;
+  if (!keeper) return;
 
   // table update: lane e = expert e
-  LayerTable *T = a.table;
-  const uint64_t tbase = *a.trace_in;
-  const bool in_range = lane < E;
-  const int slot0 = in_range ? T->expert_slot[lane] : -1;
-  uint32_t count = in_range ? T->count[lane] : 0u;
-  int64_t last = in_range ? T->last[lane] : 0;
-  int pf = in_range ? T->pf[lane] : 0;
-  const int64_t clock0 = T->clock;
-  const int64_t token0 = T->lookups;
+  if (!in_range) {
+    slot0 = -1;
+    count = 0;
+    last = 0;
+    pf = 0;
+  }
   const int n = in_range ? cnt[lane] : 0;
   const bool res_start = slot0 >= 0;
   count += (uint32_t)n;
@@ -469,7 +443,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
                                       : (uint64_t)(last + (1ll << 40));
   const int k2 = res_start ? 1 : 0;
   int above = 0;
-  for (int j = 0; j < E; ++j) {
+  for (int j = 0; j < (a.S < E ? E : 0); ++j) {  // with a slot for every expert all are kept
     const uint64_t o1 = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(k1 >> 32), j) << 32) |
                         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)k1, j);
     const int o2 = __builtin_amdgcn_readlane(k2, j);
@@ -480,8 +454,9 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
   const bool evicted = res_start && !chosen;
   // freed slots (ascending) are handed to newcomers (ascending id)
   unsigned long long freed = evicted ? (1ull << slot0) : 0ull;
+  if (a.S < E)
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) freed |= __shfl_xor(freed, o, kWave);
+    for (int o = 32; o > 0; o >>= 1) freed |= __shfl_xor(freed, o, kWave);
   const unsigned long long newmask = __ballot(newcomer);
   int slot1 = evicted ? -1 : slot0;
   int victim = -1;
@@ -507,16 +482,11 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
       wasted = 1;
   }
   const int hits = res_start ? n : 0;
-  const int misses = res_start ? 0 : n;
-  int sh = hits, sm = misses, su = useful, sw = wasted, sf = fetched ? 1 : 0;
+  int sh = hits;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    sh += __shfl_xor(sh, o, kWave);
-    sm += __shfl_xor(sm, o, kWave);
-    su += __shfl_xor(su, o, kWave);
-    sw += __shfl_xor(sw, o, kWave);
-    sf += __shfl_xor(sf, o, kWave);
-  }
+  for (int o = 32; o > 0; o >>= 1) sh += __shfl_xor(sh, o, kWave);
+  const int sm = P - sh;  // every pair is a hit or a miss
+  const int su = __popcll(__ballot(useful)), sw = __popcll(__ballot(wasted)), sf = __popcll(__ballot(fetched));
   if (in_range) {
     T->expert_slot[lane] = slot1;
     T->count[lane] = count;
@@ -768,13 +738,40 @@ __global__ __launch_bounds__(256) void prefill_unpermute_kernel(float *H, const 
 
 // ---------------------------------------------------------------------------
 // launchers used by the host engine
+int prefill_gate_splits(int T, int d) {
+  // about two workgroups a compute unit, each with at least 128 columns
+  const int blocks = (T + kGateTok - 1) / kGateTok;
+  return std::max(1, std::min((512 + blocks - 1) / blocks, d / 128));
+}
+
 hipError_t launch_prefill_gate(const PrefillArgs &a, const Launch &l) {
-  MOE_LAUNCH(prefill_gate_kernel, dim3((a.T + kGateTok - 1) / kGateTok), dim3(kGateThreads), 0, l, a);
+  const dim3 grid((a.T + kGateTok - 1) / kGateTok, a.splits);
+  if (a.d % kGateCols != 0)
+    MOE_LAUNCH((prefill_gate_kernel<true>), grid, dim3(kGateThreads), 0, l, a);
+  else
+    MOE_LAUNCH((prefill_gate_kernel<false>), grid, dim3(kGateThreads), 0, l, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_prefill_route(const PrefillArgs &a, const Launch &l) {
+  const dim3 grid((a.T + kGateTok - 1) / kGateTok), block(kGateTok * kWave);
+  if (a.d <= 512)
+    MOE_LAUNCH((prefill_route_kernel<2>), grid, block, 0, l, a);
+  else if (a.d <= 1024)
+    MOE_LAUNCH((prefill_route_kernel<4>), grid, block, 0, l, a);
+  else if (a.d <= 2048)
+    MOE_LAUNCH((prefill_route_kernel<8>), grid, block, 0, l, a);
+  else
+    MOE_LAUNCH((prefill_route_kernel<16>), grid, block, 0, l, a);
   return hipGetLastError();
 }
 
 hipError_t launch_prefill_plan(const PlanArgs &a, const Launch &l) {
-  MOE_LAUNCH(prefill_plan_kernel, dim3(1), dim3(kPlanThreads), 0, l, a);
+  // about one pair a thread; each workgroup reads every block's counts, so
+  // there are at most 64
+  const long pairs = (long)a.T * a.K;
+  const int groups = (int)std::min<long>(64, (pairs + kPlanThreads - 1) / kPlanThreads);
+  MOE_LAUNCH(prefill_plan_kernel, dim3(groups), dim3(kPlanThreads), 0, l, a);
   return hipGetLastError();
 }
 

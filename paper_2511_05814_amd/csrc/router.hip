@@ -78,25 +78,6 @@ __device__ __forceinline__ void gate_load(const RouterArgs &a, int lane, const G
   }
 }
 
-// fp64 sum over a wave's lanes, left in lane 63: running sums within rows of
-// 16 lanes (row_shr 1, 2, 4, 8), then row_bcast:15 and row_bcast:31; lanes
-// whose DPP source lies outside the pattern add 0.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ double dpp_add_d(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROW_MASK, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROW_MASK, 0xF, false);
-  return v + __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double wave_sum_d_to_lane63(double v) {
-  v = dpp_add_d<0x111, 0xF>(v);
-  v = dpp_add_d<0x112, 0xF>(v);
-  v = dpp_add_d<0x114, 0xF>(v);
-  v = dpp_add_d<0x118, 0xF>(v);
-  v = dpp_add_d<0x142, 0xA>(v);
-  v = dpp_add_d<0x143, 0xC>(v);
-  return v;
-}
-
 // The products of chunk c (whose weights are in v) into acc.
 template <int DT, int MR>
 __device__ __forceinline__ void gate_chunk(const float *hs, int d, int lane, int c, const uint4 *v, double *acc) {
@@ -273,14 +254,6 @@ __device__ int wave_victim(bool cand, int policy, int aging, int64_t clock, uint
     }
   }
   return bv ? bl : -1;
-}
-
-// Value of x on lane src, for a src the whole wave agrees on (a scalar read,
-// not an LDS round trip like a general shuffle).
-__device__ __forceinline__ int lane_value(int x, int src) { return __builtin_amdgcn_readlane(x, src); }
-__device__ __forceinline__ double lane_value_d(double x, int src) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), src),
-                          __builtin_amdgcn_readlane(__double2loint(x), src));
 }
 
 // Ring position of record base + r, from base % cap computed once.

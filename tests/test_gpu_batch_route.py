@@ -1,0 +1,44 @@
+"""GPU parity of the batched route and plan kernels at the sizes where their
+split changes: token counts around a block of 16 and around the plan's
+workgroup limit, 1 to 4 expert groups, column ranges and K tails of the gate."""
+import pytest
+
+from paper_2511_05814_amd import workload as wl
+from tests._gpu_rig import Rig, _say
+from tests.test_gpu_prefill import prefill_and_check
+
+pytestmark = pytest.mark.gpu
+
+pytest.importorskip("torch")
+
+
+def check(experts, top_k, slots, d, T, policy="lfu"):
+    cfg = wl.CONFIGS["tiny-stack"].with_(layers=1, experts=experts, top_k=top_k, d_model=d, d_ff=64, dtype="bf16", tokens=1,
+                                         prefill_tokens=T)
+    _say("route", experts, top_k, slots, d, T, policy)
+    rig = Rig(cfg)
+    moe = rig.cache(slots, policy, max_prefill_tokens=T + 3)
+    prefill_and_check(rig, moe, policy, slots, T, sorted({0, T // 2, T - 1}))
+    moe.close()
+    rig.store.close()
+
+
+@pytest.mark.parametrize("T", [1, 15, 16, 17, 255, 257, 1025])
+@pytest.mark.parametrize("experts,top_k", [(3, 1), (16, 16), (17, 4), (33, 8), (49, 5), (64, 16)])
+def test_token_and_expert_edges(T, experts, top_k):
+    # every expert resident, and (LRU, whose key needs each expert's last pair)
+    # the smallest number of slots
+    check(experts, top_k, experts, 136, T)
+    check(experts, top_k, top_k, 136, T, "lru")
+
+
+@pytest.mark.parametrize("d", [8, 40, 256, 520, 1032, 2056, 4096, 4104])
+def test_column_edges(d):
+    # one range of a few columns up to 32 ranges; rows within and beyond the
+    # columns a wave keeps in registers (512, 1024, 2048, 4096)
+    check(20, 3, 20, d, 18)
+
+
+def test_more_blocks_than_plan_workgroups():
+    # 67 x 1024 pairs: the plan kernel's 64 workgroups take more than one pair a thread
+    check(16, 16, 16, 64, 4300)
