@@ -226,10 +226,10 @@ uint64_t entropy_matrix_bytes(uint64_t n, uint64_t cap_words);
 int entropy_pack(const uint16_t *w, uint64_t n, uint64_t cap_words, uint8_t *out, uint64_t *used, const char **why);
 hipError_t launch_ffn_up(const FfnArgs &a, int dtype, const Launch &l);
 hipError_t launch_ffn_down(const FfnArgs &a, int dtype, const Launch &l);
+// Adds the partial row sums that the down launch left (ffn_down_chunks rows of
+// them; with 0 the down launch adds into h itself and there is nothing to do).
 hipError_t launch_ffn_reduce(const FfnArgs &a, int dtype, const Launch &l);
-int ffn_down_chunks(int K, int d_ff, int dtype);
-// True when launch_ffn_down also adds the partials into h (no reduce launch).
-bool ffn_down_fused(int K, int d_ff, int dtype);
+int ffn_down_chunks(int K, int d, int d_ff, int dtype);
 // group-quantised experts (dtype 2)
 hipError_t launch_ffnq_up(const FfnArgs &a, const Launch &l);
 hipError_t launch_ffnq_down(const FfnArgs &a, const Launch &l);
@@ -288,6 +288,26 @@ __device__ __forceinline__ float wave_sum(float v) {
 __device__ __forceinline__ double wave_sum_d(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+  return v;
+}
+
+// Sum over the 64 lanes of a wave, left in lane 63, through DPP moves (no LDS
+// round trips): running sums within each row of 16 lanes (row_shr 1, 2, 4,
+// 8), then lane 15 of rows 0 and 2 into rows 1 and 3 (row_bcast:15) and lane
+// 31 into rows 2 and 3 (row_bcast:31).  Lanes whose DPP source lies outside
+// the pattern add the 0 passed as the old value.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROW_MASK,
+                                                                   0xF, false));
+}
+__device__ __forceinline__ float wave_sum_to_lane63(float v) {
+  v = dpp_add<0x111, 0xF>(v);  // row_shr:1
+  v = dpp_add<0x112, 0xF>(v);  // row_shr:2
+  v = dpp_add<0x114, 0xF>(v);  // row_shr:4
+  v = dpp_add<0x118, 0xF>(v);  // row_shr:8
+  v = dpp_add<0x142, 0xA>(v);  // row_bcast:15
+  v = dpp_add<0x143, 0xC>(v);  // row_bcast:31
   return v;
 }
 

@@ -454,7 +454,7 @@ static Layout make_layout(const moe_cache *c, const moe_model_desc *d) {
   l.hostptrs = take(sizeof(void *) * c->L);
   l.err = take(256);
   l.act = take(sizeof(float) * d->top_k * (size_t)d->d_ff);
-  l.part = take(sizeof(float) * (size_t)ffn_down_chunks(d->top_k, d->d_ff, d->dtype) * d->d_model);
+  l.part = take(sizeof(float) * (size_t)ffn_down_chunks(d->top_k, d->d_model, d->d_ff, d->dtype) * d->d_model);
   const uint64_t B = expert_bytes(d);
   const uint64_t Bh_coded = coded_store(d->host_format) ? host_expert_bytes(d) : 0;
   l.prefill = take(prefill_layout(d->top_k, d->d_model, d->d_ff, c->E, c->S, d->max_prefill_tokens, B, Bh_coded).total);
@@ -855,7 +855,7 @@ static int enqueue_layer(moe_cache *c, int layer, float *h, const int32_t *inj, 
     HIP_TRY(c, kernel_span(c, c->cs, &ld, SPAN_DOWN));
     HIP_TRY(c, launch_ffn_down(f, c->dtype, ld));
     kernel_span_done(c, SPAN_DOWN, ld);
-    if (!ffn_down_fused(c->K, c->dff, c->dtype)) {
+    if (ffn_down_chunks(c->K, c->d, c->dff, c->dtype) > 0) {
       HIP_TRY(c, kernel_span(c, c->cs, &lx, SPAN_REDUCE));
       HIP_TRY(c, launch_ffn_reduce(f, c->dtype, lx));
       kernel_span_done(c, SPAN_REDUCE, lx);
@@ -1361,11 +1361,21 @@ int moe_decode_layer(moe_cache_t *c, int layer, float *h, int flags) {
   return enqueue_layer(c, layer, h, nullptr, 1, spec, c->pmax, true, workspace_scratch(c));
 }
 
+// Rows of d_model partial sums that moe_decode_layer_noalloc's limit counts:
+// one per rank, or per two 64-lane steps of a rank's row where that is longer
+// than four.  Some models write fewer or none, but which models the call takes
+// is part of its contract and does not follow the kernels' split.
+static size_t noalloc_part_rows(int K, int d_ff, int dtype) {
+  if (dtype == MOE_DTYPE_Q2G16) return (size_t)ffn_down_chunks(K, 0, d_ff, dtype);
+  const int step = kWave * (dtype == MOE_DTYPE_BF16 ? 8 : 4);
+  return (size_t)K * (d_ff <= 4 * step ? 1 : (d_ff + 2 * step - 1) / (2 * step));
+}
+
 int moe_decode_layer_noalloc(moe_cache_t *c, int layer, float *h, int flags) {
   if (!c) return fail(MOE_ERR_ARG, "NULL handle");
   if (!c->bound || !c->scratch) return fail(MOE_ERR_STATE, "handle is not bound (call moe_cache_bind)");
   const size_t act_bytes = align_up(sizeof(float) * (size_t)c->K * c->dff, 256);
-  const size_t part_bytes = align_up(sizeof(float) * (size_t)ffn_down_chunks(c->K, c->dff, c->dtype) * c->d, 256);
+  const size_t part_bytes = align_up(sizeof(float) * noalloc_part_rows(c->K, c->dff, c->dtype) * c->d, 256);
   if (act_bytes + part_bytes > kNoAllocScratchBytes)
     return fail(MOE_ERR_ARG,
                 "this model needs %zu bytes of decode scratch (top_k * d_ff activations, partial sums of d_model "

@@ -17,10 +17,13 @@
 // The down projection is split along its reduction axis (rank, column chunk)
 // so that enough workgroups stream at once; each chunk writes a partial row
 // sum and a small kernel adds the partials in a fixed order, so the result
-// does not depend on scheduling.  Narrow experts (one chunk per rank) add the
-// rank partials inside the down kernel, in the same order, instead.  Tile shapes were swept on MI355X at the
-// Mixtral (d 4096, d_ff 14336) and 64-expert (d 2048, d_ff 1408) shapes.
+// does not depend on scheduling.  Narrow experts (one chunk per rank) and
+// launches that read little add the partials inside the down kernel, also in a
+// fixed order, instead.  Tile shapes were swept on MI355X at
+// the Mixtral (d 4096, d_ff 14336) and 64-expert (d 2048, d_ff 1408) shapes.
 #include "common.hpp"
+
+#include <algorithm>
 
 namespace moe {
 namespace {
@@ -35,6 +38,7 @@ constexpr int kFusedThreads = 512;  // fused down: eight waves, one rank each
 #define MOE_FFN_DOWN_FUSED_ROWS 4
 #endif
 constexpr int kFusedRows = MOE_FFN_DOWN_FUSED_ROWS;  // rows of h per workgroup
+constexpr int kWideRowsMax = kWave;  // most rows of h per workgroup of the wide kernel
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
@@ -288,11 +292,73 @@ __global__ __launch_bounds__(kThreads) void ffn_down_kernel(FfnArgs a) {
   }
 }
 
+// down for wide experts (a rank's row longer than four 16-byte steps a lane)
+// where the whole launch reads little (see down_in_one):
+// a workgroup owns `rows` rows of h, and its eight waves share the (rank,
+// column chunk) units of those rows, wave w taking units w, w + 8, ...  A
+// wave holds its unit's g_r * act_r in registers (STEPS steps of columns) and
+// streams the unit's piece of the rows, RPW at a time, the next RPW rows'
+// loads issued before the current ones' FMAs.  Row sums stay with the wave
+// until the end, when the eight are added in wave order and into h: the order
+// is fixed, and no partial sums go to memory.  RAGGED: the last chunk of a
+// rank runs past d_ff (those columns read zeros).
+template <int DT, int STEPS, int RPW, bool RAGGED>
+__global__ __launch_bounds__(kFusedThreads) void ffn_down_wide_kernel(FfnArgs a, int rows, int cpr) {
+  using E = Elem<DT>;
+  using T = typename E::T;
+  constexpr int V = E::kVec, CH = STEPS * kWave * V, W = kFusedThreads / kWave;
+  const int d = a.d, d_ff = a.d_ff;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int row0 = blockIdx.x * rows, nrows = min(rows, d - row0);
+  __shared__ float dots[W][kWideRowsMax];
+  if (lane < nrows) dots[wave][lane] = 0.0f;
+  const int K = min(a.K, a.route->k);
+  for (int u = wave; u < K * cpr; u += W) {
+    const int rank = u / cpr, c0 = (u - rank * cpr) * CH;
+    const int slot = a.route->slot[rank];
+    if (slot < 0 || slot >= a.S) continue;
+    // this unit's columns of W2; rows past the workgroup's re-read its last
+    const T *w2 = reinterpret_cast<const T *>(a.arena + ((size_t)a.layer * a.S + slot) * a.expert_bytes) +
+                  2 * (size_t)d_ff * d + c0;
+    uint4 wa[RPW][STEPS], wb[RPW][STEPS];
+    auto load = [&](uint4 (*w)[STEPS], int r) {
+#pragma unroll
+      for (int q = 0; q < RPW; ++q)
+        load_row_strided<DT, STEPS, RAGGED>(w2, row0 + min(r + q, nrows - 1), d_ff, d_ff - c0, lane, w[q]);
+    };
+    load(wa, 0);
+    float x[STEPS][V];
+    load_x<V, STEPS, RAGGED>(a.act + (size_t)rank * d_ff + c0, d_ff - c0, lane, a.route->g[rank], x);
+    auto use = [&](const uint4 (*w)[STEPS], int r) {
+#pragma unroll
+      for (int q = 0; q < RPW; ++q) {
+        const float v = wave_sum_to_lane63(row_dot<DT, STEPS>(w[q], x));
+        if (lane == kWave - 1 && r + q < nrows) dots[wave][r + q] += v;
+      }
+    };
+    for (int r = 0; r < nrows; r += 2 * RPW) {
+      load(wb, r + RPW);
+      __builtin_amdgcn_sched_barrier(0);
+      use(wa, r);
+      __builtin_amdgcn_sched_barrier(0);
+      load(wa, r + 2 * RPW);
+      __builtin_amdgcn_sched_barrier(0);
+      use(wb, r + RPW);
+    }
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < nrows) {
+    float sum = 0.0f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) sum += dots[w][threadIdx.x];
+    a.h[row0 + threadIdx.x] += sum;
+  }
+}
+
 // down for narrow experts (each rank's row in one column chunk): the eight
 // waves of a workgroup share its RPW rows of h, wave w taking ranks w, w + 8,
-// ...; the rank partials meet in LDS and are added in rank order (the order
-// the reduction below uses) and into h, so no partial-sum buffer and no
-// second launch are needed.
+// ...; the rank partials meet in LDS and are added in rank order and into h.
 template <int DT, int STEPS, int RPW, bool RAGGED>
 __global__ __launch_bounds__(kFusedThreads) void ffn_down_fused_kernel(FfnArgs a) {
   using E = Elem<DT>;
@@ -332,8 +398,8 @@ __global__ __launch_bounds__(kFusedThreads) void ffn_down_fused_kernel(FfnArgs a
   }
 }
 
-// h += sum over chunks of the partial row sums, in chunk order; the loads of
-// eight chunks are issued together.
+// h += sum over chunks of the partial row sums, in chunk order;
+// the loads of eight chunks are issued together.
 __global__ __launch_bounds__(kReduceThreads) void ffn_reduce_kernel(const float *__restrict__ part, int nch,
                                                                     int d, float *__restrict__ h) {
   const int j = blockIdx.x * kReduceThreads + threadIdx.x;
@@ -349,17 +415,6 @@ __global__ __launch_bounds__(kReduceThreads) void ffn_reduce_kernel(const float 
   }
   for (; c < nch; ++c) sum += part[(size_t)c * d + j];
   h[j] += sum;
-}
-
-// Down tile: (column steps per chunk, rows per wave) for a given d_ff.
-struct DownShape {
-  int steps, rows;
-};
-DownShape down_shape(int d_ff, int dtype) {
-  const int cols = kWave * (dtype == 1 ? 8 : 4);
-  // narrow experts: one chunk per rank, as few padding columns as possible
-  if (d_ff <= 4 * cols) return {(d_ff + cols - 1) / cols, 2};
-  return {2, 2};
 }
 
 template <int DT, int STEPS, int RPW>
@@ -409,6 +464,36 @@ void launch_down_shape(dim3 grid, bool ragged, const FfnArgs &a, const Launch &l
     MOE_LAUNCH((ffn_down_kernel<DT, STEPS, RPW, false>), grid, dim3(kThreads), 0, l, a);
 }
 
+// Column steps of a unit of the wide kernel: the waves' longest share of the
+// K * ceil(steps / n) units, with half a step for each unit's set-up, is
+// shortest; longer units first where two are equal.
+int wide_steps(int K, int steps) {
+  int best = 8;
+  float best_cost = 0.0f;
+  for (int n = 8; n >= 1; --n) {
+    const int units = K * ((steps + n - 1) / n), rounds = (units + 7) / 8;
+    const float cost = (float)rounds * ((float)n + 0.5f);
+    if (n == 8 || cost < best_cost) {
+      best = n;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
+template <int DT, int STEPS>
+void launch_down_wide(const FfnArgs &a, const Launch &l) {
+  constexpr int CH = STEPS * kWave * Elem<DT>::kVec;
+  constexpr int RPW = STEPS <= 3 ? 2 : 1;  // rows whose loads a wave issues at once (twice that in flight)
+  const int cpr = (a.d_ff + CH - 1) / CH;
+  const int rows = std::max(2, std::min(kWideRowsMax, (a.d + 511) / 512));  // about two workgroups a CU
+  const dim3 grid((a.d + rows - 1) / rows);
+  if (a.d_ff % CH)
+    MOE_LAUNCH((ffn_down_wide_kernel<DT, STEPS, RPW, true>), grid, dim3(kFusedThreads), 0, l, a, rows, cpr);
+  else
+    MOE_LAUNCH((ffn_down_wide_kernel<DT, STEPS, RPW, false>), grid, dim3(kFusedThreads), 0, l, a, rows, cpr);
+}
+
 template <int DT, int STEPS>
 void launch_down_fused(bool ragged, const FfnArgs &a, const Launch &l) {
   const dim3 grid((a.d + kFusedRows - 1) / kFusedRows);
@@ -418,22 +503,29 @@ void launch_down_fused(bool ragged, const FfnArgs &a, const Launch &l) {
     MOE_LAUNCH((ffn_down_fused_kernel<DT, STEPS, kFusedRows, false>), grid, dim3(kFusedThreads), 0, l, a);
 }
 
-#ifndef MOE_FFN_DOWN_FUSE
-#define MOE_FFN_DOWN_FUSE 1
-#endif
+constexpr int kChunkSteps = 2;  // column steps per chunk of the chunked kernel
 
-bool down_fused(int K, int d_ff, int dtype) {
-  if (!MOE_FFN_DOWN_FUSE || (dtype != 0 && dtype != 1)) return false;
-  const int cols = kWave * (dtype == 1 ? 8 : 4);
-  return K <= kMaxK && d_ff <= 4 * cols;
+// Does one down launch do the whole projection?  Narrow experts always.  Wide
+// ones when the launch reads at most 24 MiB: it is then bound by launches, and
+// the reduction's costs 2.6 us; above, many short (rank, chunk) workgroups
+// stream faster than long-lived waves do.  A decode step on bf16 experts, us
+// with the chunks and the reduction / in one launch: 2 of d 256, d_ff 4096 (4
+// MiB) 18.9 / 16.4; 2 of 1024 x 4096 (16 MiB) 19.2 / 16.4; 4 of 1024 x 4096 (32
+// MiB) 20.0 / 20.4; 4 of 512 x 14336 (56 MiB) 29.0 / 31.7; 2 of 4096 x 14336
+// (224 MiB) 100 / 103.
+constexpr long kDownInOneBytes = 24l << 20;
+bool down_in_one(int K, int d, int d_ff, int dtype) {
+  const int elem = dtype == 1 ? 2 : 4, step = kWave * (16 / elem);
+  return d_ff <= 4 * step || (long)K * d * d_ff * elem <= kDownInOneBytes;
 }
 
 template <int DT>
 hipError_t launch_down_t(const FfnArgs &a, const Launch &l) {
-  const DownShape sh = down_shape(a.d_ff, DT);
-  if (down_fused(a.K, a.d_ff, DT)) {
-    const bool ragged = a.d_ff % (sh.steps * kWave * Elem<DT>::kVec) != 0;
-    switch (sh.steps) {
+  constexpr int COLS = kWave * Elem<DT>::kVec;
+  const int steps = (a.d_ff + COLS - 1) / COLS;
+  if (steps <= 4) {  // one chunk per rank, as few padding columns as possible
+    const bool ragged = a.d_ff % COLS != 0;
+    switch (steps) {
       case 1: launch_down_fused<DT, 1>(ragged, a, l); break;
       case 2: launch_down_fused<DT, 2>(ragged, a, l); break;
       case 3: launch_down_fused<DT, 3>(ragged, a, l); break;
@@ -441,25 +533,31 @@ hipError_t launch_down_t(const FfnArgs &a, const Launch &l) {
     }
     return hipGetLastError();
   }
-  const int rows = kWavesPerBlock * sh.rows;
-  const int ch = sh.steps * kWave * Elem<DT>::kVec;
-  const dim3 grid(((a.d + rows - 1) / rows) * ffn_down_chunks(a.K, a.d_ff, DT));
-  switch (sh.steps) {
-    case 1: launch_down_shape<DT, 1, 2>(grid, a.d_ff % ch != 0, a, l); break;
-    case 2: launch_down_shape<DT, 2, 2>(grid, a.d_ff % ch != 0, a, l); break;
-    case 3: launch_down_shape<DT, 3, 2>(grid, a.d_ff % ch != 0, a, l); break;
-    default: launch_down_shape<DT, 4, 2>(grid, a.d_ff % ch != 0, a, l); break;
+  if (!down_in_one(a.K, a.d, a.d_ff, DT)) {
+    const int rows = kWavesPerBlock * 2, ch = kChunkSteps * COLS;
+    const dim3 grid(((a.d + rows - 1) / rows) * ffn_down_chunks(a.K, a.d, a.d_ff, DT));
+    launch_down_shape<DT, kChunkSteps, 2>(grid, a.d_ff % ch != 0, a, l);
+    return hipGetLastError();
+  }
+  switch (wide_steps(a.K, steps)) {
+    case 1: launch_down_wide<DT, 1>(a, l); break;
+    case 2: launch_down_wide<DT, 2>(a, l); break;
+    case 3: launch_down_wide<DT, 3>(a, l); break;
+    case 4: launch_down_wide<DT, 4>(a, l); break;
+    case 5: launch_down_wide<DT, 5>(a, l); break;
+    case 6: launch_down_wide<DT, 6>(a, l); break;
+    case 7: launch_down_wide<DT, 7>(a, l); break;
+    default: launch_down_wide<DT, 8>(a, l); break;
   }
   return hipGetLastError();
 }
 
 }  // namespace
 
-bool ffn_down_fused(int K, int d_ff, int dtype) { return down_fused(K, d_ff, dtype); }
-
-int ffn_down_chunks(int K, int d_ff, int dtype) {
+int ffn_down_chunks(int K, int d, int d_ff, int dtype) {
   if (dtype == 2) return ffnq_down_chunks(K, d_ff);
-  const int ch = down_shape(d_ff, dtype).steps * kWave * (dtype == 1 ? 8 : 4);
+  if (down_in_one(K, d, d_ff, dtype)) return 0;
+  const int ch = kChunkSteps * kWave * (dtype == 1 ? 8 : 4);
   return K * ((d_ff + ch - 1) / ch);
 }
 
@@ -475,7 +573,7 @@ hipError_t launch_ffn_down(const FfnArgs &a, int dtype, const Launch &l) {
 
 hipError_t launch_ffn_reduce(const FfnArgs &a, int dtype, const Launch &l) {
   MOE_LAUNCH(ffn_reduce_kernel, dim3((a.d + kReduceThreads - 1) / kReduceThreads), dim3(kReduceThreads), 0, l,
-             (const float *)a.part, ffn_down_chunks(a.K, a.d_ff, dtype), a.d, a.h);
+             (const float *)a.part, ffn_down_chunks(a.K, a.d, a.d_ff, dtype), a.d, a.h);
   return hipGetLastError();
 }
 

@@ -127,26 +127,6 @@ __device__ __forceinline__ float unit_dot(const QUnit &u, const float *x, const 
 
 __device__ __forceinline__ float silu(float v) { return v / (1.0f + __expf(-v)); }
 
-// Sum over the 64 lanes of a wave, left in lane 63, through DPP moves (no LDS
-// round trips): running sums within each row of 16 lanes (row_shr 1, 2, 4,
-// 8), then lane 15 of rows 0 and 2 into rows 1 and 3 (row_bcast:15) and lane
-// 31 into rows 2 and 3 (row_bcast:31).  Lanes whose DPP source lies outside
-// the pattern add the 0 passed as the old value.
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ float dpp_add(float v) {
-  return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROW_MASK,
-                                                                   0xF, false));
-}
-__device__ __forceinline__ float wave_sum_to_lane63(float v) {
-  v = dpp_add<0x111, 0xF>(v);  // row_shr:1
-  v = dpp_add<0x112, 0xF>(v);  // row_shr:2
-  v = dpp_add<0x114, 0xF>(v);  // row_shr:4
-  v = dpp_add<0x118, 0xF>(v);  // row_shr:8
-  v = dpp_add<0x142, 0xA>(v);  // row_bcast:15
-  v = dpp_add<0x143, 0xC>(v);  // row_bcast:31
-  return v;
-}
-
 // act_r = SiLU(W1_r x) * (W3_r x), x = h / rms(h); d <= STEPS * 4096.
 // G workgroups per rank; each wave walks row groups of RPW rows with a stride
 // of G * 4 groups, loading the next group's weights before it works on the
