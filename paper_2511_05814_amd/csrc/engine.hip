@@ -810,14 +810,17 @@ static int enqueue_layer(moe_cache *c, int layer, float *h, const int32_t *inj, 
     }
     int rc = issue_fetch(c, c->dl + layer, 0, qd);
     if (rc != MOE_OK) return rc;
-    if (!c->one_stream) {
+    // Copies on the compute stream are ordered by it; only speculative copies,
+    // which queue behind this layer's demand copies, need their event.  (An
+    // event nobody waits for costs a marker packet between the copy kernel and
+    // the FFN: a step of the tiny fp32 model takes 18.2 us a layer without it, 20.0
+    // with.)
+    if (!c->one_stream && !(demand_on_cs && spec_layer < 0)) {
       HIP_TRY(c, hipEventRecord(c->ev_demand[layer], qd));
-      if (demand_on_cs) {
-        // speculative copies queue behind this layer's demand copies
-        if (spec_layer >= 0) HIP_TRY(c, hipStreamWaitEvent(q, c->ev_demand[layer], 0));
-      } else {
+      if (demand_on_cs)
+        HIP_TRY(c, hipStreamWaitEvent(q, c->ev_demand[layer], 0));
+      else
         c->demand_pending[layer] = 1;
-      }
     }
   }
   if (spec_layer >= 0 && !split && !no_copies) {
