@@ -188,8 +188,8 @@ __global__ __launch_bounds__(kThreads) void ffn_up_kernel(FfnArgs a) {
   for (int q = 0; q < RPW; ++q) {
     if (q + 1 < RPW) load_row<DT, STEPS, RAGGED>(w, min(row0 + q + 1, d_ff - 1), d, lane, u[(q + 1) & 1]);
     __builtin_amdgcn_sched_barrier(0);
-    const float r = wave_sum(row_dot<DT, STEPS>(u[q & 1], x));
-    if (lane == 0) dots[wave][q] = r;
+    const float r = wave_sum_to_lane63(row_dot<DT, STEPS>(u[q & 1], x));
+    if (lane == kWave - 1) dots[wave][q] = r;
   }
   __syncthreads();
   if (threadIdx.x < kRows && base + (int)threadIdx.x < d_ff) {
@@ -287,8 +287,8 @@ __global__ __launch_bounds__(kThreads) void ffn_down_kernel(FfnArgs a) {
   }
 #pragma unroll
   for (int q = 0; q < RPW; ++q) {
-    const float s = wave_sum(acc[q]);
-    if (lane == 0 && row0 + q < d) a.part[(size_t)ch * d + row0 + q] = s;
+    const float s = wave_sum_to_lane63(acc[q]);
+    if (lane == kWave - 1 && row0 + q < d) a.part[(size_t)ch * d + row0 + q] = s;
   }
 }
 
@@ -386,8 +386,8 @@ __global__ __launch_bounds__(kFusedThreads) void ffn_down_fused_kernel(FfnArgs a
     }
 #pragma unroll
     for (int q = 0; q < RPW; ++q) {
-      const float s = wave_sum(acc[q]);
-      if (lane == 0) dots[rank][q] = s;
+      const float s = wave_sum_to_lane63(acc[q]);
+      if (lane == kWave - 1) dots[rank][q] = s;
     }
   }
   __syncthreads();

@@ -256,7 +256,7 @@ __device__ int wave_victim(bool cand, int policy, int aging, int64_t clock, uint
   return bv ? bl : -1;
 }
 
-// Ring position of record base + r, from base % cap computed once.
+// Ring position of record base + r, from base_pos = base % cap.
 __device__ __forceinline__ uint64_t ring_pos(uint64_t base_pos, int r, uint64_t cap, int K) {
   uint64_t pos = base_pos + (uint64_t)r;
   if (pos >= cap) pos = cap >= (uint64_t)K ? pos - cap : pos % cap;
@@ -280,7 +280,7 @@ __device__ void put_rec(const RouterArgs &a, uint64_t pos, int kind, int64_t tok
 
 // Wave 0: the token's K lookups in layer a.layer, in rank order.
 // `idreg` on lane r < K holds the expert of rank r.
-__device__ void demand_lookup(const RouterArgs &a, int idreg, int lane, uint64_t rec_base, const TableView &tv) {
+__device__ void demand_lookup(const RouterArgs &a, int idreg, int lane, uint64_t base_pos, const TableView &tv) {
   LayerTable *T = a.tables + a.layer;
   LayerStats *st = a.stats + a.layer;
   FetchList *fl = a.dlists + a.layer;
@@ -296,7 +296,6 @@ __device__ void demand_lookup(const RouterArgs &a, int idreg, int lane, uint64_t
   int my_rank = -1;  // the rank that selected this lane's expert (ids are distinct)
   for (int r = 0; r < K; ++r) my_rank = lane_value(idreg, r) == lane ? r : my_rank;
   const bool pinned = my_rank >= 0;
-  const uint64_t base_pos = a.trace_cap ? rec_base % a.trace_cap : 0;
 
   // Rank lane r's expert: its slot and prefetched flag before the lookups.
   const int j_l = lane < K ? idreg : 0;
@@ -405,7 +404,7 @@ __device__ void demand_lookup(const RouterArgs &a, int idreg, int lane, uint64_t
 
 // Wave 1: insert up to pmax of the K guesses (lane r holds rank r's guess)
 // into the table of a.spec_layer, all guesses pinned.
-__device__ void prefetch_insert(const RouterArgs &a, int greg, int lane, uint64_t rec_base, const TableView &tv) {
+__device__ void prefetch_insert(const RouterArgs &a, int greg, int lane, uint64_t base_pos, const TableView &tv) {
   const int L2 = a.spec_layer;
   LayerTable *T = a.tables + L2;
   LayerStats *st = a.stats + L2;
@@ -421,7 +420,6 @@ __device__ void prefetch_insert(const RouterArgs &a, int greg, int lane, uint64_
 
   bool pinned = false;
   for (int r = 0; r < K; ++r) pinned |= (lane_value(greg, r) == lane);
-  const uint64_t base_pos = a.trace_cap ? rec_base % a.trace_cap : 0;
 
   // Every guess already resident: nothing to insert, only the records.
   const int slot_l = __shfl(my_slot, lane < K ? greg : 0, kWave);
@@ -537,10 +535,10 @@ template <int MR>
 __global__ __launch_bounds__(kThreads) void router_kernel(RouterArgs a) {
   __shared__ __align__(16) float hs[kMaxD];
   __shared__ double zs[2 * kMaxE];
-  __shared__ int s_top[2][kMaxK];
+  __shared__ int s_top[3][kMaxK];
   __shared__ double red[kWaves];
   __shared__ int s_cnt[2][kRankParts][kMaxE];
-  __shared__ uint64_t s_tbase;
+  __shared__ uint64_t s_tbase, s_tpos[2];
   __shared__ int s_demand_ok;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int E = a.E, d = a.d;
@@ -582,8 +580,6 @@ __global__ __launch_bounds__(kThreads) void router_kernel(RouterArgs a) {
       ss = fma((double)v.z, (double)v.z, ss);
       ss = fma((double)v.w, (double)v.w, ss);
     }
-    ss = wave_sum_d(ss);
-    if (lane == 0) red[wave] = ss;
     __syncthreads();
     if (gw.m > 0) {  // the same for the whole wave
       if (a.dtype == 1)
@@ -591,24 +587,35 @@ __global__ __launch_bounds__(kThreads) void router_kernel(RouterArgs a) {
       else
         gate_logits<0, MR>(a, hs, lane, gw, gv, zs);
     }
+    ss = wave_sum_d_to_lane63(ss);  // not needed before the softmax
+    if (lane == kWave - 1) red[wave] = ss;
   }
   __syncthreads();
   rank_parts(zs, E, route_here, spec, tid, s_cnt);
+  // a wave of the set that is not ranked finds the records' ring positions
+  // (64-bit remainders) meanwhile: [0] the demand records, [1] the guesses
+  if (wave == (spec ? kWaves / 2 - 1 : kWaves - 1) && lane < 2 && a.trace_cap)
+    s_tpos[lane] = (s_tbase + (lane == 1 && a.demand ? (uint64_t)a.K : 0)) % a.trace_cap;
   __syncthreads();
 
+  // The softmax is only needed by the FFN, so a wave of its own computes it
+  // while wave 0 does the lookups: renormalised softmax over the selected
+  // logits z / rms (rank 0 is the max).
+  if (wave == 2 && route_here) {
+    const int id = topk_from_parts(s_cnt[0], E, a.K, lane, s_top[2]);
+    const double zr = (lane < a.K) ? zs[id < 0 ? 0 : id] : 0.0;
+    const double ss = lane_value_d(wave_sum_d_to_lane63(lane < kWaves ? red[lane] : 0.0), kWave - 1);
+    const double r = sqrt(ss / (double)d + 1e-5);
+    const double z0 = lane_value_d(zr, 0);
+    const double ex = (lane < a.K) ? exp((zr - z0) / r) : 0.0;
+    const double den = lane_value_d(wave_sum_d_to_lane63(ex), kWave - 1);
+    if (lane < a.K) a.route->g[lane] = (float)(ex / den);
+    if (lane == 0) a.route->inv_r = (float)(1.0 / r);
+  }
   if (wave == 0 && demand) {
     int idreg;
     if (route_here) {
       idreg = topk_from_parts(s_cnt[0], E, a.K, lane, s_top[0]);
-      // renormalised softmax over the selected logits z / rms (rank 0 is the max)
-      const double zr = (lane < a.K) ? zs[idreg < 0 ? 0 : idreg] : 0.0;
-      const double ss = lane_value_d(wave_sum_d_to_lane63(lane < kWaves ? red[lane] : 0.0), kWave - 1);
-      const double r = sqrt(ss / (double)d + 1e-5);
-      const double z0 = lane_value_d(zr, 0);
-      const double ex = (lane < a.K) ? exp((zr - z0) / r) : 0.0;
-      const double den = lane_value_d(wave_sum_d_to_lane63(ex), kWave - 1);
-      if (lane < a.K) a.route->g[lane] = (float)(ex / den);
-      if (lane == 0) a.route->inv_r = (float)(1.0 / r);
     } else {
       idreg = (lane < a.K) ? a.inj_ids[lane] : -1;
       bool ok = true;
@@ -631,13 +638,13 @@ __global__ __launch_bounds__(kThreads) void router_kernel(RouterArgs a) {
       }
     }
     if (lane_value(idreg, 0) >= 0) {
-      demand_lookup(a, idreg, lane, s_tbase, tv);
+      demand_lookup(a, idreg, lane, s_tpos[0], tv);
       if (lane == 0) s_demand_ok = 1;
     }
   }
   if (wave == 1 && spec) {
     const int greg = topk_from_parts(s_cnt[1], E, a.K, lane, s_top[1]);
-    prefetch_insert(a, greg, lane, s_tbase + (a.demand ? (uint64_t)a.K : 0), tv);
+    prefetch_insert(a, greg, lane, s_tpos[1], tv);
   }
   __syncthreads();
   // the demand workgroup (or the only one) advances the count past both roles'
