@@ -7,9 +7,9 @@
 // Weights are stored out x in, so both operands are K-major.  A tile is up to
 // 256 sorted rows of one expert by 256 weight rows (128 output features of W1
 // and of W3 in the up projection, 256 of W2 in the down projection; half as
-// many in the narrow form).  Four waves, one a SIMD: each owns a quarter of
-// the weight rows and all MX 32-row blocks of the tile (MX = 1 .. 8 is a
-// template parameter, so a tile costs what its rows need, to 32 rows).
+// many in the narrow form).  Four waves, one a SIMD, share its products; the
+// number of 32-row blocks (MX = 1 .. 8) is a template parameter, so a tile
+// costs what its rows need, to 32 rows.
 //
 // Both operands are staged by the memory system (loads straight into LDS) in
 // slices of 64 columns, whole 128-byte lines, into rings of three slices (two
@@ -105,10 +105,19 @@ __device__ __forceinline__ void gemm_tile(const GemmTile &t, const uint16_t *a_s
   constexpr int NA = 3, NB = 3 * (AB + BB) <= LDS ? 3 : 2;  // slices in the rings
   static_assert(NA * AB + NB * BB <= LDS, "the rings fit");
   constexpr int BN = (UP ? 64 : 128) * NY;           // output features of the tile
-  constexpr int WB = 32 * NY;                        // weight rows of a wave: y 0 and 1 from W1 and W3 in the up projection
+  // The waves form a WM x (4 / WM) grid over (row blocks, weight rows): XW row
+  // blocks by YW 32-row weight blocks each, in the up projection YM of W1 and
+  // the same features' YM of W3.
+  // Two by two where the tile is tall (XW, YW 4, 4 instead of 8, 2: eight
+  // fragment reads per sixteen products instead of ten), else every wave has
+  // all row blocks, so that a tile costs what its rows need; 4096 tokens of
+  // top-8 over 64 experts 709 / 704 us, of top-4 over 16 (d_ff 4096) 863 / 858.
+  constexpr int WM = NY == 2 && MX % 2 == 0 && MX >= 6 ? 2 : 1;
+  constexpr int XW = MX / WM, YW = NY * WM, YM = UP && NY == 2 ? YW / 2 : YW;
   constexpr int IA = MX, IB = 4 * NY;                // a wave's load instructions per slice
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int wm = wave % WM, wn = wave / WM;
   const int K = UP ? d : d_ff, N = UP ? d_ff : d;
 
   // sources: load instruction i of the wave fills slice rows 8 (4 i + wave) ..
@@ -147,30 +156,28 @@ __device__ __forceinline__ void gemm_tile(const GemmTile &t, const uint16_t *a_s
   };
 
   // fragments: lane i holds row i % 32 of a block, columns 16 h + 8 (i / 32) .. + 7
-  // of part h.  In the up projection a wave's y = 0 rows are of W1 and its
-  // y = 1 rows the same features of W3 (NY = 1: 16 rows of each in one block).
+  // of part h.  (Narrow up tiles: 16 rows of W1 and 16 of W3 in one block.)
   const int r32 = lane & 31, hi = lane >> 5, sw = (r32 >> 1) & 7;
-  const uint32_t fa = r32 * kRowB + ((hi ^ sw) << 4);
+  const uint32_t fa = (wm * XW * 32 + r32) * kRowB + ((hi ^ sw) << 4);
   constexpr bool kMixed = UP && NY == 1;
-  const int brow = kMixed ? (r32 < 16 ? 16 * wave + r32 : 64 + 16 * wave + r32 - 16) : (UP ? 32 : WB) * wave + r32;
+  const int brow = kMixed ? (r32 < 16 ? 16 * wn + r32 : 64 + 16 * wn + r32 - 16) : 32 * YM * wn + r32;
   const uint32_t fb = NA * AB + brow * kRowB + ((hi ^ ((brow >> 1) & 7)) << 4);
-  constexpr int YB = (UP ? 128 : 32) * kRowB;
   struct Frags {
-    bf16x8 a[MX], b[NY];
+    bf16x8 a[XW], b[YW];
   };
-  constexpr int NF = MX + NY;
+  constexpr int NF = XW + YW;
   auto rd = [&](Frags &f, int i, uint32_t at_a, uint32_t at_b, int h) {
-    if (i < NY)
-      f.b[i] = frag(lds + ((fb + at_b) ^ (h << 5)) + i * YB);
+    if (i < YW)
+      f.b[i] = frag(lds + ((fb + at_b) ^ (h << 5)) + (i / YM * 128 + i % YM * 32) * kRowB);
     else
-      f.a[i - NY] = frag(lds + ((fa + at_a) ^ (h << 5)) + (i - NY) * kBlockB);
+      f.a[i - YW] = frag(lds + ((fa + at_a) ^ (h << 5)) + (i - YW) * kBlockB);
   };
 
-  floatx16 c[MX][NY];
+  floatx16 c[XW][YW];
 #pragma unroll
-  for (int x = 0; x < MX; ++x)
+  for (int x = 0; x < XW; ++x)
 #pragma unroll
-    for (int y = 0; y < NY; ++y)
+    for (int y = 0; y < YW; ++y)
 #pragma unroll
       for (int i = 0; i < 16; ++i) c[x][y][i] = 0.0f;
 
@@ -205,7 +212,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTile &t, const uint16_t *a_s
 #define MOE_PART(F, G, ATA, ATB, H, COUNT, LOAD)                                                         \
   _Pragma("unroll") for (int m = 0; m < M2; ++m) {                                                       \
     _Pragma("unroll") for (int i = 0; i < NF; ++i) if (i / 2 == m || (m == M2 - 1 && i / 2 > m)) rd(G, i, ATA, ATB, H); \
-    c[m / NY][m % NY] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.b[m % NY], F.a[m / NY], c[m / NY][m % NY], 0, 0, 0);  \
+    c[m / YW][m % YW] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.b[m % YW], F.a[m / YW], c[m / YW][m % YW], 0, 0, 0);  \
     __builtin_amdgcn_sched_barrier(0);                                                                   \
     _Pragma("unroll") for (int q = 0; q < (COUNT); ++q)                                                  \
       if (q * M2 / (COUNT) == m) {                                                                       \
@@ -244,30 +251,33 @@ __device__ __forceinline__ void gemm_tile(const GemmTile &t, const uint16_t *a_s
 
   // a lane holds row lane % 32 of each block and its features 8 g + 4 (lane / 32) + 0 .. 3
 #pragma unroll
-  for (int x = 0; x < MX; ++x) {
-    if (x * 32 + r32 >= t.rows) continue;
-    const size_t row = (size_t)(t.row + x * 32 + r32) * N;
+  for (int x = 0; x < XW; ++x) {
+    const int m = (wm * XW + x) * 32 + r32;
+    if (m >= t.rows) continue;
+    const size_t row = (size_t)(t.row + m) * N;
     if (UP) {
       uint16_t *o = static_cast<uint16_t *>(out) + row;
-      constexpr int G = kMixed ? 2 : 4;  // groups of four features a wave's W1 rows make
+      constexpr int G = kMixed ? 2 : 4;  // groups of four features a block of W1 rows makes
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const int n = t.n0 + 8 * G * wave + 8 * g + 4 * hi;
-        if (n < N) {
-          uint32_t v[4];
+      for (int y = 0; y < (kMixed ? 1 : YM); ++y)
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
-            v[i] = bf16_rne(silu(c[x][0][4 * g + i]) * (kMixed ? c[x][0][8 + 4 * g + i] : c[x][NY - 1][4 * g + i]));
-          *reinterpret_cast<u32x2 *>(o + n) = u32x2{v[0] | (v[1] << 16), v[2] | (v[3] << 16)};
+        for (int g = 0; g < G; ++g) {
+          const int n = t.n0 + 8 * G * (wn * (kMixed ? 1 : YM) + y) + 8 * g + 4 * hi;
+          if (n < N) {
+            uint32_t v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              v[i] = bf16_rne(silu(c[x][y][4 * g + i]) * (kMixed ? c[x][0][8 + 4 * g + i] : c[x][YW - YM + y][4 * g + i]));
+            *reinterpret_cast<u32x2 *>(o + n) = u32x2{v[0] | (v[1] << 16), v[2] | (v[3] << 16)};
+          }
         }
-      }
     } else {
       float *o = static_cast<float *>(out) + row;
 #pragma unroll
-      for (int y = 0; y < NY; ++y)
+      for (int y = 0; y < YW; ++y)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
-          const int n = t.n0 + WB * wave + 32 * y + 8 * g + 4 * hi;
+          const int n = t.n0 + 32 * (YW * wn + y) + 8 * g + 4 * hi;
           if (n < N)
             *reinterpret_cast<floatx4 *>(o + n) =
                 floatx4{c[x][y][4 * g], c[x][y][4 * g + 1], c[x][y][4 * g + 2], c[x][y][4 * g + 3]};
