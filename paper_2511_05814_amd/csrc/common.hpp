@@ -235,9 +235,9 @@ hipError_t launch_ffnq_up(const FfnArgs &a, const Launch &l);
 hipError_t launch_ffnq_down(const FfnArgs &a, const Launch &l);
 int ffnq_down_chunks(int K, int d_ff);
 hipError_t launch_prefill_gate(const PrefillArgs &a, const Launch &l);
-hipError_t launch_prefill_route(const PrefillArgs &a, const Launch &l);
 int prefill_gate_splits(int T, int d);  // column ranges of a batch's gate launch
-hipError_t launch_prefill_plan(const PlanArgs &a, const Launch &l);
+// Top-K, weights and rows of every token, then the batch's plan.
+hipError_t launch_prefill_route_plan(const PrefillArgs &a, const PlanArgs &p, const Launch &l);
 // Grouped GEMMs over a tile list (wide tiles: up to kWideRows rows by
 // prefill_tile_cols(up, true) output columns; narrow ones up to kNarrowRows by
 // half as many).  With ntiles the list's length is read on the device (at most

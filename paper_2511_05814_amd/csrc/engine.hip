@@ -972,7 +972,6 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   ga.K = c->K;
   ga.splits = prefill_gate_splits(T, c->d);
   HIP_TRY(c, launch_prefill_gate(ga, Launch{c->cs}));
-  HIP_TRY(c, launch_prefill_route(ga, Launch{c->cs}));
   PlanArgs pa{};
   pa.ids = ids;
   pa.blk_cnt = ga.blk_cnt;
@@ -1017,7 +1016,7 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   }
   pa.arena_layer = arena + (size_t)layer * c->S * c->B;
   pa.slot_bytes = c->B;
-  HIP_TRY(c, launch_prefill_plan(pa, Launch{c->cs}));
+  HIP_TRY(c, launch_prefill_route_plan(ga, pa, Launch{c->cs}));
   c->tpar ^= 1;
   if (on_device) {
     const double rows = (double)pairs;

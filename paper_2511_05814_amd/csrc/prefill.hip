@@ -159,14 +159,21 @@ __global__ __launch_bounds__(kGateThreads) void prefill_gate_kernel(PrefillArgs 
 // last (token, rank) pair that did, from which the plan kernel's workgroups
 // find their places without passing over all pairs.  The row's loads are
 // issued first and stay in registers up to 256 * NV columns.
+struct RouteShared {
+  double zs[kGateTok][kMaxE];
+  int top[kGateTok][kMaxK];
+  int cnt[kMaxE], last[kMaxE];
+};
+
 template <int NV>
-__global__ __launch_bounds__(kGateTok *kWave) void prefill_route_kernel(PrefillArgs a) {
-  __shared__ double zs[kGateTok][kMaxE];
-  __shared__ int s_top[kGateTok][kMaxK];
-  __shared__ int s_cnt[kMaxE], s_last[kMaxE];
+__device__ __forceinline__ void route_block(const PrefillArgs &a, int blk, RouteShared &sh) {
+  auto &zs = sh.zs;
+  auto &s_top = sh.top;
+  auto &s_cnt = sh.cnt;
+  auto &s_last = sh.last;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int d = a.d, E = a.E, K = a.K;
-  const int t = blockIdx.x * kGateTok + wave;
+  const int t = blk * kGateTok + wave;
   if (tid < kMaxE) {
     s_cnt[tid] = 0;
     s_last[tid] = 0;
@@ -233,9 +240,15 @@ __global__ __launch_bounds__(kGateTok *kWave) void prefill_route_kernel(PrefillA
   }
   __syncthreads();
   if (tid < kMaxE) {
-    a.blk_cnt[(size_t)blockIdx.x * kMaxE + tid] = (uint8_t)s_cnt[tid];   // at most 16: a token names an expert once
-    a.blk_last[(size_t)blockIdx.x * kMaxE + tid] = (uint8_t)s_last[tid];  // below 16 * 16
+    a.blk_cnt[(size_t)blk * kMaxE + tid] = (uint8_t)s_cnt[tid];   // at most 16: a token names an expert once
+    a.blk_last[(size_t)blk * kMaxE + tid] = (uint8_t)s_last[tid];  // below 16 * 16
   }
+}
+
+template <int NV>
+__global__ __launch_bounds__(kGateTok *kWave) void prefill_route_kernel(PrefillArgs a) {
+  __shared__ RouteShared sh;
+  route_block<NV>(a, blockIdx.x, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -255,38 +268,68 @@ constexpr int kPlanThreads = 1024;
 constexpr int kPlanWaves = kPlanThreads / kWave;
 constexpr int kPlanAhead = 8;  // blocks' counts in flight per wave
 
-__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) {
-  __shared__ int part[3][kPlanWaves][kMaxE];  // totals, totals before this share, last pair + 1
-  __shared__ int cnt[kMaxE], cur[kMaxE], lastp[kMaxE], offs[kMaxE];
+struct PlanShared {
+  int part[3][kPlanWaves][kMaxE];  // totals, totals before this share, last pair + 1
+  int cnt[kMaxE], cur[kMaxE], lastp[kMaxE], offs[kMaxE];
   // tile lists (when a.ntiles): cost of each row-block size, the expert's
   // first tile and rows per tile in each list, the lists' lengths
-  __shared__ float tcost[2][kWideRows / 32];
-  __shared__ int tfirst[2][kMaxE], trows[2][kMaxE], tlen[2];
-  __shared__ const uint16_t *tw[kMaxE];  // the experts' weights (when a.tiles)
-  __shared__ int bad;
+  float tcost[2][kWideRows / 32];
+  int tfirst[2][kMaxE], trows[2][kMaxE], tlen[2];
+  const uint16_t *tw[kMaxE];  // the experts' weights (when a.tiles)
+  int bad;
+};
+
+// Lane e's view of the layer's table, and the trace's length: what the plan
+// needs that no other kernel of the batch writes.
+struct PlanTable {
+  int slot0, pf;
+  uint32_t count;
+  int64_t last, clock0, token0;
+  uint64_t tbase;
+};
+
+__device__ __forceinline__ PlanTable plan_table(const PlanArgs &a, bool keeper) {
+  const LayerTable *T = a.table;
+  const int le = min((int)(threadIdx.x & (kWave - 1)), a.E - 1);
+  PlanTable p{};
+  p.slot0 = T->expert_slot[le];
+  if (keeper) {
+    p.count = T->count[le];
+    p.last = T->last[le];
+    p.pf = T->pf[le];
+    p.clock0 = T->clock;
+    p.token0 = T->lookups;
+    p.tbase = *a.trace_in;
+  }
+  return p;
+}
+
+// Share g of G of the plan; pt loaded before (keeper: g == 0, first wave).
+__device__ __forceinline__ void plan_share(const PlanArgs &a, int g, int G, const PlanTable &pt, PlanShared &sh) {
+  auto &part = sh.part;
+  auto &cnt = sh.cnt;
+  auto &cur = sh.cur;
+  auto &lastp = sh.lastp;
+  auto &offs = sh.offs;
+  auto &tcost = sh.tcost;
+  auto &tfirst = sh.tfirst;
+  auto &trows = sh.trows;
+  auto &tlen = sh.tlen;
+  auto &tw = sh.tw;
+  int &bad = sh.bad;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int E = a.E, P = a.T * a.K;
   const int nblk = (a.T + kGateTok - 1) / kGateTok;
-  const int b0 = (int)((long)nblk * blockIdx.x / gridDim.x), b1 = (int)((long)nblk * (blockIdx.x + 1) / gridDim.x);
-  // everything that depends on nothing is loaded first: the table (workgroup
-  // 0's first wave), the first of this share's ids and the blocks' counts
+  const int b0 = (int)((long)nblk * g / G), b1 = (int)((long)nblk * (g + 1) / G);
   LayerTable *T = a.table;
   const bool in_range = lane < E;
-  const bool keeper = wave == 0 && blockIdx.x == 0;  // the wave that updates the table
-  const int le = min(lane, E - 1);
-  int slot0 = T->expert_slot[le];
-  uint32_t count = 0;
-  int64_t last = 0, clock0 = 0, token0 = 0;
-  int pf = 0;
-  uint64_t tbase = 0;
-  if (keeper) {
-    count = T->count[le];
-    last = T->last[le];
-    pf = T->pf[le];
-    clock0 = T->clock;
-    token0 = T->lookups;
-    tbase = *a.trace_in;
-  }
+  const bool keeper = wave == 0 && g == 0;  // the wave that updates the table
+  int slot0 = pt.slot0, pf = pt.pf;
+  uint32_t count = pt.count;
+  int64_t last = pt.last;
+  const int64_t clock0 = pt.clock0, token0 = pt.token0;
+  const uint64_t tbase = pt.tbase;
+  // the first of this share's ids and the blocks' counts
   const int p_lo = b0 * kGateTok * a.K, p_hi = min(P, b1 * kGateTok * a.K);
   const int id0 = p_lo < p_hi ? a.ids[min(p_lo + tid, p_hi - 1)] : 0;
   if (tid == 0) bad = 0;
@@ -297,7 +340,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
     for (int u = 0; u < kPlanAhead; ++u) {
       const size_t at = (size_t)min(b + u * kPlanWaves, nblk - 1) * kMaxE + lane;
       c[u] = a.blk_cnt[at];
-      l[u] = blockIdx.x == 0 ? a.blk_last[at] : 0;  // only the table needs it
+      l[u] = g == 0 ? a.blk_last[at] : 0;  // only the table needs it
     }
 #pragma unroll
     for (int u = 0; u < kPlanAhead; ++u) {
@@ -389,7 +432,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
       if (lane == kWave - 1) {
         const bool fits = it <= tl.cap && !bad;  // the host's bound holds for any counts
         tlen[li] = fits ? it : 0;
-        if (blockIdx.x == 0) {
+        if (g == 0) {
           a.ntiles[li] = tlen[li];
           if (!fits) *a.err = ERR_BAD_LIST;
         }
@@ -398,7 +441,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
     __syncthreads();
     // tile i of a list belongs to the last expert whose first tile is <= i
     const int nup = tlen[0], n_all = tlen[0] + tlen[1];
-    for (int i = blockIdx.x * kPlanThreads + tid; i < n_all; i += gridDim.x * kPlanThreads) {
+    for (int i = g * kPlanThreads + tid; i < n_all; i += G * kPlanThreads) {
       const int list = i < nup ? 0 : 1;
       const int li = list == 0 ? i : i - nup;
       int lo = 0, hi = E - 1;
@@ -482,10 +525,10 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
       wasted = 1;
   }
   const int hits = res_start ? n : 0;
-  int sh = hits;
+  int all_hits = hits;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) sh += __shfl_xor(sh, o, kWave);
-  const int sm = P - sh;  // every pair is a hit or a miss
+  for (int o = 32; o > 0; o >>= 1) all_hits += __shfl_xor(all_hits, o, kWave);
+  const int sm = P - all_hits;  // every pair is a hit or a miss
   const int su = __popcll(__ballot(useful)), sw = __popcll(__ballot(wasted)), sf = __popcll(__ballot(fetched));
   if (in_range) {
     T->expert_slot[lane] = slot1;
@@ -519,7 +562,7 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
     T->lookups = token0 + a.T;
     *a.trace_out = tbase + (a.trace && a.trace_cap ? (uint64_t)E : 0);
     LayerStats *st = a.stats;
-    st->v[ST_HITS] += sh;
+    st->v[ST_HITS] += all_hits;
     st->v[ST_MISSES] += sm;
     st->v[ST_EVICT] += n_new;
     st->v[ST_PF_USEFUL] += su;
@@ -527,6 +570,30 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
     st->v[ST_LOOKUPS] += a.T;
     st->v[ST_BYTES] += (uint64_t)sf * a.expert_bytes;
   }
+}
+
+__global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) {
+  __shared__ PlanShared sh;
+  const PlanTable pt = plan_table(a, threadIdx.x < kWave && blockIdx.x == 0);
+  plan_share(a, blockIdx.x, gridDim.x, pt, sh);
+}
+
+// Both for a batch of at most two blocks, in one workgroup: small batches are
+// bound by launches (a batch of a few small experts takes 38 us with six
+// launches, 41 with seven).
+constexpr int kRoutePlanBlocks = 2;
+static_assert(kPlanThreads == kGateTok * kWave, "one workgroup does both");
+
+template <int NV>
+__global__ __launch_bounds__(kPlanThreads) void prefill_route_plan_kernel(PrefillArgs a, PlanArgs p) {
+  __shared__ RouteShared rs;
+  __shared__ PlanShared ps;
+  const PlanTable pt = plan_table(p, threadIdx.x < kWave);
+  for (int blk = 0; blk * kGateTok < a.T; ++blk) {
+    route_block<NV>(a, blk, rs);
+    __syncthreads();  // the block's ids and counts are written; its LDS is free
+  }
+  plan_share(p, 0, 1, pt, ps);
 }
 
 // ---------------------------------------------------------------------------
@@ -753,25 +820,30 @@ hipError_t launch_prefill_gate(const PrefillArgs &a, const Launch &l) {
   return hipGetLastError();
 }
 
-hipError_t launch_prefill_route(const PrefillArgs &a, const Launch &l) {
-  const dim3 grid((a.T + kGateTok - 1) / kGateTok), block(kGateTok * kWave);
-  if (a.d <= 512)
-    MOE_LAUNCH((prefill_route_kernel<2>), grid, block, 0, l, a);
-  else if (a.d <= 1024)
-    MOE_LAUNCH((prefill_route_kernel<4>), grid, block, 0, l, a);
-  else if (a.d <= 2048)
-    MOE_LAUNCH((prefill_route_kernel<8>), grid, block, 0, l, a);
-  else
-    MOE_LAUNCH((prefill_route_kernel<16>), grid, block, 0, l, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_prefill_plan(const PlanArgs &a, const Launch &l) {
-  // about one pair a thread; each workgroup reads every block's counts, so
-  // there are at most 64
+hipError_t launch_prefill_route_plan(const PrefillArgs &a, const PlanArgs &p, const Launch &l) {
+  const int blocks = (a.T + kGateTok - 1) / kGateTok;
+  // one pair a thread or less in most batches; each workgroup of the plan
+  // reads every block's counts, so there are at most 64
   const long pairs = (long)a.T * a.K;
-  const int groups = (int)std::min<long>(64, (pairs + kPlanThreads - 1) / kPlanThreads);
-  MOE_LAUNCH(prefill_plan_kernel, dim3(groups), dim3(kPlanThreads), 0, l, a);
+  const int shares = (int)std::min<long>(64, (pairs + kPlanThreads - 1) / kPlanThreads);
+#define MOE_ROUTE(NV)                                                                                   \
+  do {                                                                                                  \
+    if (blocks <= kRoutePlanBlocks) {                                                                   \
+      MOE_LAUNCH((prefill_route_plan_kernel<NV>), dim3(1), dim3(kPlanThreads), 0, l, a, p);             \
+    } else {                                                                                            \
+      MOE_LAUNCH((prefill_route_kernel<NV>), dim3(blocks), dim3(kGateTok * kWave), 0, l, a);            \
+      MOE_LAUNCH(prefill_plan_kernel, dim3(shares), dim3(kPlanThreads), 0, l, p);                       \
+    }                                                                                                   \
+  } while (0)
+  if (a.d <= 512)
+    MOE_ROUTE(2);
+  else if (a.d <= 1024)
+    MOE_ROUTE(4);
+  else if (a.d <= 2048)
+    MOE_ROUTE(8);
+  else
+    MOE_ROUTE(16);
+#undef MOE_ROUTE
   return hipGetLastError();
 }
 
