@@ -112,7 +112,8 @@ struct PrefillPlan {
 // expert whose weights are at w, by the output columns from n0 on.
 struct GemmTile {
   const uint16_t *w;  // expert base (W1 | W3 | W2), bf16
-  int32_t row, rows, n0, pad;
+  int32_t row, rows, n0;
+  int32_t once;       // these are all of the expert's rows: the launch reads its weights once
 };
 constexpr int kWideRows = 256, kNarrowRows = 64;  // most rows of a wide and of a narrow tile
 

@@ -1105,7 +1105,7 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
     if (nt >= p.tile_cap)
       overflow = true;
     else
-      ht[nt++] = GemmTile{weights[e], pl[e].off + m0, rows, n0, 0};
+      ht[nt++] = GemmTile{weights[e], pl[e].off + m0, rows, n0, rows == pl[e].n};
   };
   auto add_tiles = [&](const std::vector<int> &group, long rows, bool up, int &first, int &count, bool &wide) {
     const int ncols = up ? c->dff : c->d;

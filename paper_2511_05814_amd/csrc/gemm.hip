@@ -41,6 +41,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 constexpr int kThreads = 256;
+constexpr int kOnceBlocks = 5;     // most row blocks of a tile with a non-temporal form
 constexpr int kKs = 64;            // columns of a slice
 constexpr int kRowB = kKs * 2;     // bytes of a slice row: one 128-byte line
 constexpr int kBlockB = 32 * kRowB;  // bytes of 32 slice rows
@@ -71,9 +72,15 @@ __device__ __forceinline__ float silu(float v) {
 // own waits (wait_vm) are the only ones.  M0 carries the LDS address; the
 // compiler sets M0 itself before any instruction of its own that reads it
 // (none in this kernel: gfx9 LDS instructions do not use it).
+// ONCE: non-temporal.
+template <bool ONCE>
 __device__ __forceinline__ void dma_weights(__amdgpu_buffer_rsrc_t r, uint32_t m0, uint32_t voff, uint32_t soff) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               : : "s"(__builtin_amdgcn_readfirstlane(m0)), "v"(voff), "s"(r), "s"(__builtin_amdgcn_readfirstlane(soff)) : "memory");
+  if constexpr (ONCE)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen nt lds"
+                 : : "s"(__builtin_amdgcn_readfirstlane(m0)), "v"(voff), "s"(r), "s"(__builtin_amdgcn_readfirstlane(soff)) : "memory");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+                 : : "s"(__builtin_amdgcn_readfirstlane(m0)), "v"(voff), "s"(r), "s"(__builtin_amdgcn_readfirstlane(soff)) : "memory");
 }
 __device__ __forceinline__ void dma_rows(const void *p, uint32_t m0) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
@@ -98,7 +105,12 @@ __device__ __forceinline__ bf16x8 frag(const uint8_t *p) {
 // c ^ ((r / 2) % 8), so the 16 lanes the LDS serves at once in a fragment read
 // (16 rows at one chunk) touch all 64 banks once.  A load instruction fills
 // eight rows, lane i fetching the chunk that the swizzle puts at its place.
-template <bool UP, bool RAGGED, int MX, int NY, int LDS>
+// ONCE: the tile has all of its expert's rows, so no other reads its weights
+// and they are loaded non-temporally: 32 tokens of top-8 over 64 experts 176 ->
+// 152 us, 509 tokens 250 -> 232.  Weights that several tiles share in L2 lose by
+// it: with every load so 4096 tokens take 740 us instead of 704, 2048 tokens of
+// top-2 over 8 experts 1523 instead of 1477.
+template <bool UP, bool RAGGED, int MX, bool ONCE, int NY, int LDS>
 __device__ __forceinline__ void gemm_tile(const GemmTile &t, const uint16_t *a_src, const int32_t *perm_tok, void *out,
                                           int d, int d_ff, uint8_t *lds) {
   constexpr int AB = MX * kBlockB, BB = NY * 4 * kBlockB;  // bytes of an A and of a B slice
@@ -150,9 +162,9 @@ __device__ __forceinline__ void gemm_tile(const GemmTile &t, const uint16_t *a_s
     const uint32_t so = (uint32_t)s * kRowB;
     const __amdgpu_buffer_rsrc_t r = brs[UP ? i / (IB / 2) : 0];
     if (RAGGED)
-      dma_weights(r, m0b + at + i * kBlockB, s * kKs + 8 * lc >= K ? kOobOffset : boff[i] + so, 0);
+      dma_weights<ONCE>(r, m0b + at + i * kBlockB, s * kKs + 8 * lc >= K ? kOobOffset : boff[i] + so, 0);
     else
-      dma_weights(r, m0b + at + i * kBlockB, boff[i], so);
+      dma_weights<ONCE>(r, m0b + at + i * kBlockB, boff[i], so);
   };
 
   // fragments: lane i holds row i % 32 of a block, columns 16 h + 8 (i / 32) .. + 7
@@ -321,8 +333,14 @@ __global__ __launch_bounds__(kThreads, WIDE ? 1 : 2) void prefill_gemm_kernel(co
   if ((int)blockIdx.x >= nt) return;
   const GemmTile t = tiles[xcd_tile(blockIdx.x, nt)];
   if (t.rows <= 0 || t.rows > (WIDE ? kWideRows : kNarrowRows)) return;  // the planners make no such tiles
-#define MOE_CASE(M) \
-  case M: gemm_tile<UP, RAGGED, M, WIDE ? 2 : 1, LDS>(t, a_src, perm_tok, out, d, d_ff, lds); break;
+  // (from six row blocks on a tile is bound by its products either way)
+#define MOE_CASE(M)                                                                                      \
+  case M:                                                                                                \
+    if (M <= kOnceBlocks && t.once)                                                                      \
+      gemm_tile<UP, RAGGED, M, M <= kOnceBlocks, WIDE ? 2 : 1, LDS>(t, a_src, perm_tok, out, d, d_ff, lds); \
+    else                                                                                                 \
+      gemm_tile<UP, RAGGED, M, false, WIDE ? 2 : 1, LDS>(t, a_src, perm_tok, out, d, d_ff, lds);         \
+    break;
   if constexpr (WIDE) {
     switch ((t.rows + 31) / 32) {
       MOE_CASE(1) MOE_CASE(2) MOE_CASE(3) MOE_CASE(4) MOE_CASE(5) MOE_CASE(6) MOE_CASE(7) MOE_CASE(8)

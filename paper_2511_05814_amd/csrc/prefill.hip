@@ -456,10 +456,11 @@ __device__ __forceinline__ void plan_share(const PlanArgs &a, int g, int G, cons
       const int k = li - tfirst[list][lo];
       const int cb = k / nt, mb = k - cb * nt;
       a.tiles[(list == 0 ? a.up.first : a.dn.first) + li] =
-          GemmTile{tw[lo], offs[lo] + mb * per, min(per, cnt[lo] - mb * per), cb * (list == 0 ? a.up.cols : a.dn.cols), 0};
+          GemmTile{tw[lo], offs[lo] + mb * per, min(per, cnt[lo] - mb * per), cb * (list == 0 ? a.up.cols : a.dn.cols),
+                   nt == 1};
     }
   } else if (a.tiles && keeper && in_range) {
-    a.tiles[lane] = GemmTile{tw[lane], offs[lane], bad ? 0 : cnt[lane], 0, 0};
+    a.tiles[lane] = GemmTile{tw[lane], offs[lane], bad ? 0 : cnt[lane], 0, 1};
     if (bad) *a.err = ERR_BAD_LIST;
   }
   if (!keeper) return;

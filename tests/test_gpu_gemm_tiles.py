@@ -50,3 +50,19 @@ def test_small_and_ragged_tiles(d, d_ff):
     # tail), partial column blocks, narrow tiles (at most 48 rows an expert)
     # and, from 49 rows on, wide ones
     check(d, d_ff, 3, [17, 31, 48, 49, 100])
+
+
+@pytest.mark.parametrize("T", [300, 384])
+@pytest.mark.parametrize("slots", [2, 8])
+def test_experts_of_one_and_of_several_short_tiles(T, slots):
+    # one expert a token, chosen unevenly: at most 48 rows an expert on average,
+    # so narrow tiles, of which experts with more than 64 rows take several
+    # (weights read by more than one tile) and the others one
+    cfg = wl.CONFIGS["tiny-stack"].with_(layers=1, experts=8, top_k=1, d_model=136, d_ff=192, dtype="bf16", tokens=1,
+                                         prefill_tokens=T)
+    _say("short tiles", T, slots)
+    rig = Rig(cfg)
+    moe = rig.cache(slots, "lfu", max_prefill_tokens=T)
+    prefill_and_check(rig, moe, "lfu", slots, T, list(range(0, T, 7)))
+    moe.close()
+    rig.store.close()
