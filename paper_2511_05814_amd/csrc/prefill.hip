@@ -579,10 +579,16 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
   plan_share(a, blockIdx.x, gridDim.x, pt, sh);
 }
 
-// Both for a batch of at most two blocks, in one workgroup: small batches are
-// bound by launches (a batch of a few small experts takes 38 us with six
-// launches, 41 with seven).
-constexpr int kRoutePlanBlocks = 2;
+// Both for a batch of one block of a narrow model, in one workgroup: such
+// batches are bound by launches (us a pass with one launch / two, 16 tokens: 15
+// experts of d 256 40.8 / 42.2, 32 of d 1024 45.7 / 47.0, 64 of d 2048 82.8 /
+// 83.4).  Two blocks would run one after the other on one compute unit (24
+// tokens: 15 of d 256 44.5 / 43.0, 32 of d 1024 48.0 / 44.8, 64 of d 2048 80.3 /
+// 73.8, 8 of d 4096 79.7 / 68.7), and rows of more than 2048 columns do not fit
+// the registers of a 1024-thread workgroup beside the table: held all the same
+// they spill (16 tokens of 8 experts of d 4096 66.4 us), read again they cost
+// more than the launch saves (57.9 / 56.8; d 8192 89.8 / 87.9).
+constexpr int kRoutePlanCols = 2048;
 static_assert(kPlanThreads == kGateTok * kWave, "one workgroup does both");
 
 template <int NV>
@@ -590,10 +596,8 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_route_plan_kernel(Prefil
   __shared__ RouteShared rs;
   __shared__ PlanShared ps;
   const PlanTable pt = plan_table(p, threadIdx.x < kWave);
-  for (int blk = 0; blk * kGateTok < a.T; ++blk) {
-    route_block<NV>(a, blk, rs);
-    __syncthreads();  // the block's ids and counts are written; its LDS is free
-  }
+  route_block<NV>(a, 0, rs);
+  __syncthreads();  // the block's ids and counts are written
   plan_share(p, 0, 1, pt, ps);
 }
 
@@ -823,19 +827,18 @@ hipError_t launch_prefill_gate(const PrefillArgs &a, const Launch &l) {
 
 hipError_t launch_prefill_route_plan(const PrefillArgs &a, const PlanArgs &p, const Launch &l) {
   const int blocks = (a.T + kGateTok - 1) / kGateTok;
-  // one pair a thread or less in most batches; each workgroup of the plan
-  // reads every block's counts, so there are at most 64
-  const long pairs = (long)a.T * a.K;
-  const int shares = (int)std::min<long>(64, (pairs + kPlanThreads - 1) / kPlanThreads);
-#define MOE_ROUTE(NV)                                                                                   \
-  do {                                                                                                  \
-    if (blocks <= kRoutePlanBlocks) {                                                                   \
-      MOE_LAUNCH((prefill_route_plan_kernel<NV>), dim3(1), dim3(kPlanThreads), 0, l, a, p);             \
-    } else {                                                                                            \
-      MOE_LAUNCH((prefill_route_kernel<NV>), dim3(blocks), dim3(kGateTok * kWave), 0, l, a);            \
-      MOE_LAUNCH(prefill_plan_kernel, dim3(shares), dim3(kPlanThreads), 0, l, p);                       \
-    }                                                                                                   \
-  } while (0)
+  if (blocks == 1 && a.d <= kRoutePlanCols) {
+#define MOE_ROUTE(NV) MOE_LAUNCH((prefill_route_plan_kernel<NV>), dim3(1), dim3(kPlanThreads), 0, l, a, p)
+    if (a.d <= 512)
+      MOE_ROUTE(2);
+    else if (a.d <= 1024)
+      MOE_ROUTE(4);
+    else
+      MOE_ROUTE(8);
+#undef MOE_ROUTE
+    return hipGetLastError();
+  }
+#define MOE_ROUTE(NV) MOE_LAUNCH((prefill_route_kernel<NV>), dim3(blocks), dim3(kGateTok * kWave), 0, l, a)
   if (a.d <= 512)
     MOE_ROUTE(2);
   else if (a.d <= 1024)
@@ -845,6 +848,11 @@ hipError_t launch_prefill_route_plan(const PrefillArgs &a, const PlanArgs &p, co
   else
     MOE_ROUTE(16);
 #undef MOE_ROUTE
+  // one pair a thread or less in most batches; each workgroup of the plan
+  // reads every block's counts, so there are at most 64
+  const long pairs = (long)a.T * a.K;
+  const int shares = (int)std::min<long>(64, (pairs + kPlanThreads - 1) / kPlanThreads);
+  MOE_LAUNCH(prefill_plan_kernel, dim3(shares), dim3(kPlanThreads), 0, l, p);
   return hipGetLastError();
 }
 

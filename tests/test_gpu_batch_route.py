@@ -39,6 +39,18 @@ def test_column_edges(d):
     check(20, 3, 20, d, 18)
 
 
+@pytest.mark.parametrize("T", [1, 13, 16])
+@pytest.mark.parametrize("d", [40, 512, 520, 1024, 1032, 2048, 2056, 4104])
+def test_one_block(d, T):
+    # at most 16 tokens: route and plan in one launch up to 2048 columns (rows
+    # held in 2, 4 or 8 registers a lane), in two above.  40 columns at least:
+    # rounding x and act to bf16 alone puts a row of 40 off by 2.9e-3 (median)
+    # and 5.6e-3 (one in 1000), a row of 8, whose few errors do not average, by
+    # 2.9e-3 and 1.2e-2 (fp64 arithmetic on N(0, 0.02^2) weights), against a
+    # bound of 6e-3
+    check(20, 3, 20, d, T)
+
+
 def test_more_blocks_than_plan_workgroups():
     # 67 x 1024 pairs: the plan kernel's 64 workgroups take more than one pair a thread
     check(16, 16, 16, 64, 4300)
