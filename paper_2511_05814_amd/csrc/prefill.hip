@@ -153,102 +153,137 @@ __global__ __launch_bounds__(kGateThreads) void prefill_gate_kernel(PrefillArgs 
   }
 }
 
-// One wave per token: the partial logits added in order, rms in fp64, top-K by
-// rank counting, renormalised softmax weights and the normalised bf16 row; a
-// workgroup's 16 tokens also leave how many of them chose each expert and the
-// last (token, rank) pair that did, from which the plan kernel's workgroups
-// find their places without passing over all pairs.  The row's loads are
-// issued first and stay in registers up to 256 * NV columns.
+// One wave per token of a block: the partial logits added in order, rms in
+// fp64, top-K by rank counting, renormalised softmax weights and the
+// normalised bf16 row; a block's 16 tokens also leave how many of them chose
+// each expert and the last (token, rank) pair that did, from which the plan
+// kernel's workgroups find their places without passing over all pairs.  The
+// row's loads are issued first and stay in registers up to 256 * NV columns.
+// With TB blocks a wave takes one token of each, side by side: the chain of a
+// token's steps is latency, which the other fills.
+template <int TB>
 struct RouteShared {
-  double zs[kGateTok][kMaxE];
-  int top[kGateTok][kMaxK];
-  int cnt[kMaxE], last[kMaxE];
+  double zs[TB][kGateTok][kMaxE];
+  int top[TB][kGateTok][kMaxK];
+  int cnt[TB][kMaxE], last[TB][kMaxE];
 };
 
-template <int NV>
-__device__ __forceinline__ void route_block(const PrefillArgs &a, int blk, RouteShared &sh) {
-  auto &zs = sh.zs;
-  auto &s_top = sh.top;
-  auto &s_cnt = sh.cnt;
-  auto &s_last = sh.last;
+template <int NV, int TB>
+__device__ __forceinline__ void route_blocks(const PrefillArgs &a, int blk0, RouteShared<TB> &sh) {
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int d = a.d, E = a.E, K = a.K;
-  const int t = blk * kGateTok + wave;
-  if (tid < kMaxE) {
-    s_cnt[tid] = 0;
-    s_last[tid] = 0;
+  for (int x = tid; x < TB * kMaxE; x += kGateTok * kWave) {
+    sh.cnt[x / kMaxE][x % kMaxE] = 0;
+    sh.last[x / kMaxE][x % kMaxE] = 0;
   }
   __syncthreads();
-  if (t < a.T) {  // the same for the whole wave
-    const float *row = a.H + (size_t)t * d;
-    float4 v[NV];
+  int t[TB];
+  bool live[TB];  // the same for the whole wave
+  const float *row[TB];
 #pragma unroll
-    for (int u = 0; u < NV; ++u) v[u] = *reinterpret_cast<const float4 *>(row + min(u * 256 + lane * 4, d - 4));
-    const double *zr0 = a.zpart + (size_t)t * kMaxE + min(lane, E - 1);
+  for (int q = 0; q < TB; ++q) {
+    t[q] = (blk0 + q) * kGateTok + wave;
+    live[q] = t[q] < a.T;
+    row[q] = a.H + (size_t)min(t[q], a.T - 1) * d;  // past T: the last token again, unused
+  }
+  if (live[0]) {  // blocks are in token order: with none in the first there is none in the second
+    float4 v[TB][NV];
+#pragma unroll
+    for (int q = 0; q < TB; ++q)
+#pragma unroll
+      for (int u = 0; u < NV; ++u) v[q][u] = *reinterpret_cast<const float4 *>(row[q] + min(u * 256 + lane * 4, d - 4));
     const size_t zstride = (size_t)a.T * kMaxE;
     constexpr int kAhead = 8;  // partial logits in flight (clamped past the last, unused)
-    double zv[kAhead];
+    const double *zr0[TB];
+    double zv[TB][kAhead], z[TB];
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) zv[u] = zr0[min(u, a.splits - 1) * zstride];
-    double z = zv[0];
+    for (int q = 0; q < TB; ++q) {
+      zr0[q] = a.zpart + (size_t)min(t[q], a.T - 1) * kMaxE + min(lane, E - 1);
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u) zv[q][u] = zr0[q][min(u, a.splits - 1) * zstride];
+      z[q] = zv[q][0];
+    }
     for (int s0 = 0; s0 < a.splits; s0 += kAhead) {
 #pragma unroll
-      for (int u = 0; u < kAhead; ++u) {
-        if (s0 + u > 0) z += s0 + u < a.splits ? zv[u] : 0.0;
-        zv[u] = zr0[min(s0 + u + kAhead, a.splits - 1) * zstride];
-      }
-    }
-    zs[wave][lane] = z;
-    double sq = 0.0;
-    auto square = [&](const float4 &q) {
-      sq = fma((double)q.x, (double)q.x, sq);
-      sq = fma((double)q.y, (double)q.y, sq);
-      sq = fma((double)q.z, (double)q.z, sq);
-      sq = fma((double)q.w, (double)q.w, sq);
-    };
+      for (int u = 0; u < kAhead; ++u)
 #pragma unroll
-    for (int u = 0; u < NV; ++u)
-      if (u * 256 + lane * 4 < d) square(v[u]);
-    for (int c = NV * 256 + lane * 4; c < d; c += 256) square(*reinterpret_cast<const float4 *>(row + c));
-    const double rr = sqrt(lane_value_d(wave_sum_d_to_lane63(sq), kWave - 1) / (double)d + 1e-5);
+        for (int q = 0; q < TB; ++q) {
+          if (s0 + u > 0) z[q] += s0 + u < a.splits ? zv[q][u] : 0.0;
+          zv[q][u] = zr0[q][min(s0 + u + kAhead, a.splits - 1) * zstride];
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < TB; ++q) sh.zs[q][wave][lane] = z[q];
+    auto square = [](double &sq, const float4 &x) {
+      sq = fma((double)x.x, (double)x.x, sq);
+      sq = fma((double)x.y, (double)x.y, sq);
+      sq = fma((double)x.z, (double)x.z, sq);
+      sq = fma((double)x.w, (double)x.w, sq);
+    };
+    double rr[TB];
+#pragma unroll
+    for (int q = 0; q < TB; ++q) {
+      double sq = 0.0;
+#pragma unroll
+      for (int u = 0; u < NV; ++u)
+        if (u * 256 + lane * 4 < d) square(sq, v[q][u]);
+      for (int c = NV * 256 + lane * 4; c < d; c += 256) square(sq, *reinterpret_cast<const float4 *>(row[q] + c));
+      rr[q] = sqrt(lane_value_d(wave_sum_d_to_lane63(sq), kWave - 1) / (double)d + 1e-5);
+    }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int mine = wave_topk_lds(zs[wave], E, K, lane, s_top[wave]);
-    const double zr = lane < K ? zs[wave][mine] : 0.0;
-    const double z0 = lane_value_d(zr, 0);
-    const double ex = lane < K ? exp((zr - z0) / rr) : 0.0;
-    const double den = lane_value_d(wave_sum_d_to_lane63(ex), kWave - 1);
-    if (lane < K) {
-      a.ids[(size_t)t * K + lane] = mine;
-      a.g[(size_t)t * K + lane] = (float)(ex / den);
-      atomicAdd(&s_cnt[mine], 1);
-      atomicMax(&s_last[mine], wave * K + lane);
-    }
-    const float inv = (float)(1.0 / rr);
-    uint16_t *xr = a.xn + (size_t)t * d;
-    auto put = [&](const float4 &q, int c) {
-      uint2 o;
-      o.x = (uint32_t)f32_to_bf16_rne(q.x * inv) | ((uint32_t)f32_to_bf16_rne(q.y * inv) << 16);
-      o.y = (uint32_t)f32_to_bf16_rne(q.z * inv) | ((uint32_t)f32_to_bf16_rne(q.w * inv) << 16);
-      *reinterpret_cast<uint2 *>(xr + c) = o;
-    };
+    const double *zq[TB];
+    int *tq[TB], mine[TB];
 #pragma unroll
-    for (int u = 0; u < NV; ++u)
-      if (u * 256 + lane * 4 < d) put(v[u], u * 256 + lane * 4);
-    for (int c = NV * 256 + lane * 4; c < d; c += 256) put(*reinterpret_cast<const float4 *>(row + c), c);
+    for (int q = 0; q < TB; ++q) {
+      zq[q] = sh.zs[q][wave];
+      tq[q] = sh.top[q][wave];
+    }
+    wave_topk_lds<TB>(zq, E, K, lane, tq, mine);
+#pragma unroll
+    for (int q = 0; q < TB; ++q) {
+      const double zr = lane < K ? zq[q][mine[q]] : 0.0;
+      const double z0 = lane_value_d(zr, 0);
+      const double ex = lane < K ? exp((zr - z0) / rr[q]) : 0.0;
+      const double den = lane_value_d(wave_sum_d_to_lane63(ex), kWave - 1);
+      if (live[q] && lane < K) {
+        a.ids[(size_t)t[q] * K + lane] = mine[q];
+        a.g[(size_t)t[q] * K + lane] = (float)(ex / den);
+        atomicAdd(&sh.cnt[q][mine[q]], 1);
+        atomicMax(&sh.last[q][mine[q]], wave * K + lane);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < TB; ++q) {
+      if (!live[q]) continue;
+      const float inv = (float)(1.0 / rr[q]);
+      uint16_t *xr = a.xn + (size_t)t[q] * d;
+      auto put = [&](const float4 &x, int c) {
+        uint2 o;
+        o.x = (uint32_t)f32_to_bf16_rne(x.x * inv) | ((uint32_t)f32_to_bf16_rne(x.y * inv) << 16);
+        o.y = (uint32_t)f32_to_bf16_rne(x.z * inv) | ((uint32_t)f32_to_bf16_rne(x.w * inv) << 16);
+        *reinterpret_cast<uint2 *>(xr + c) = o;
+      };
+#pragma unroll
+      for (int u = 0; u < NV; ++u)
+        if (u * 256 + lane * 4 < d) put(v[q][u], u * 256 + lane * 4);
+      for (int c = NV * 256 + lane * 4; c < d; c += 256) put(*reinterpret_cast<const float4 *>(row[q] + c), c);
+    }
   }
   __syncthreads();
-  if (tid < kMaxE) {
-    a.blk_cnt[(size_t)blk * kMaxE + tid] = (uint8_t)s_cnt[tid];   // at most 16: a token names an expert once
-    a.blk_last[(size_t)blk * kMaxE + tid] = (uint8_t)s_last[tid];  // below 16 * 16
+  for (int x = tid; x < TB * kMaxE; x += kGateTok * kWave) {
+    const int q = x / kMaxE, e = x % kMaxE;
+    if ((blk0 + q) * kGateTok >= a.T) break;
+    a.blk_cnt[(size_t)(blk0 + q) * kMaxE + e] = (uint8_t)sh.cnt[q][e];   // at most 16: a token names an expert once
+    a.blk_last[(size_t)(blk0 + q) * kMaxE + e] = (uint8_t)sh.last[q][e];  // below 16 * 16
   }
 }
 
 template <int NV>
 __global__ __launch_bounds__(kGateTok *kWave) void prefill_route_kernel(PrefillArgs a) {
-  __shared__ RouteShared sh;
-  route_block<NV>(a, blockIdx.x, sh);
+  __shared__ RouteShared<1> sh;
+  route_blocks<NV, 1>(a, blockIdx.x, sh);
 }
 
 // ---------------------------------------------------------------------------
@@ -579,25 +614,30 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
   plan_share(a, blockIdx.x, gridDim.x, pt, sh);
 }
 
-// Both for a batch of one block of a narrow model, in one workgroup: such
-// batches are bound by launches (us a pass with one launch / two, 16 tokens: 15
-// experts of d 256 40.8 / 42.2, 32 of d 1024 45.7 / 47.0, 64 of d 2048 82.8 /
-// 83.4).  Two blocks would run one after the other on one compute unit (24
-// tokens: 15 of d 256 44.5 / 43.0, 32 of d 1024 48.0 / 44.8, 64 of d 2048 80.3 /
-// 73.8, 8 of d 4096 79.7 / 68.7), and rows of more than 2048 columns do not fit
-// the registers of a 1024-thread workgroup beside the table: held all the same
-// they spill (16 tokens of 8 experts of d 4096 66.4 us), read again they cost
-// more than the launch saves (57.9 / 56.8; d 8192 89.8 / 87.9).
-constexpr int kRoutePlanCols = 2048;
+// Both for a batch of one or two blocks of a narrow model, in one workgroup:
+// such batches are bound by launches.  us with one launch / two: 16 tokens of
+// 15 experts of d 256 40.8 / 42.2, of 32 of d 1024 45.7 / 47.0, of 64 of d 2048
+// 82.8 / 83.4; 24 tokens of 4 experts of d 1024 34.7 / 42.1, of 32 of d 256
+// 38.9 / 42.6.  Two blocks cost more there than in workgroups of their own
+// (eight layers in turn, where the host keeps ahead: 4 experts of d 1024 238 /
+// 231 us, 32 of d 256 268 / 253), with many experts more than the launch saves
+// (64 of d 256 44.2 / 42.4 and 330 / 297); one after the other they cost 48.7
+// and 364 there.  Rows of more than 2048 columns (two blocks': 1024) do not fit
+// the registers of a 1024-thread workgroup: held all the same they spill (16
+// tokens of 8 experts of d 4096 66.4 us), read again they cost more than the
+// launch saves (57.9 / 56.8; d 8192 89.8 / 87.9).
+constexpr bool route_plan_in_one(int blocks, int d, int E) {
+  return (blocks == 1 && d <= 2048) || (blocks == 2 && d <= 1024 && E <= 32);
+}
 static_assert(kPlanThreads == kGateTok * kWave, "one workgroup does both");
 
-template <int NV>
+template <int NV, int TB>
 __global__ __launch_bounds__(kPlanThreads) void prefill_route_plan_kernel(PrefillArgs a, PlanArgs p) {
-  __shared__ RouteShared rs;
+  __shared__ RouteShared<TB> rs;
   __shared__ PlanShared ps;
   const PlanTable pt = plan_table(p, threadIdx.x < kWave);
-  route_block<NV>(a, 0, rs);
-  __syncthreads();  // the block's ids and counts are written
+  route_blocks<NV, TB>(a, 0, rs);
+  __syncthreads();  // the blocks' ids and counts are written
   plan_share(p, 0, 1, pt, ps);
 }
 
@@ -827,14 +867,18 @@ hipError_t launch_prefill_gate(const PrefillArgs &a, const Launch &l) {
 
 hipError_t launch_prefill_route_plan(const PrefillArgs &a, const PlanArgs &p, const Launch &l) {
   const int blocks = (a.T + kGateTok - 1) / kGateTok;
-  if (blocks == 1 && a.d <= kRoutePlanCols) {
-#define MOE_ROUTE(NV) MOE_LAUNCH((prefill_route_plan_kernel<NV>), dim3(1), dim3(kPlanThreads), 0, l, a, p)
-    if (a.d <= 512)
-      MOE_ROUTE(2);
+  if (route_plan_in_one(blocks, a.d, a.E)) {
+#define MOE_ROUTE(NV, TB) MOE_LAUNCH((prefill_route_plan_kernel<NV, TB>), dim3(1), dim3(kPlanThreads), 0, l, a, p)
+    if (blocks == 2 && a.d <= 512)
+      MOE_ROUTE(2, 2);
+    else if (blocks == 2)
+      MOE_ROUTE(4, 2);
+    else if (a.d <= 512)
+      MOE_ROUTE(2, 1);
     else if (a.d <= 1024)
-      MOE_ROUTE(4);
+      MOE_ROUTE(4, 1);
     else
-      MOE_ROUTE(8);
+      MOE_ROUTE(8, 1);
 #undef MOE_ROUTE
     return hipGetLastError();
   }

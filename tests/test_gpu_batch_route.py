@@ -51,6 +51,14 @@ def test_one_block(d, T):
     check(20, 3, 20, d, T)
 
 
+@pytest.mark.parametrize("T", [17, 31, 32])
+@pytest.mark.parametrize("experts,d", [(20, 40), (32, 512), (20, 520), (32, 1024), (20, 1032), (33, 520)])
+def test_two_blocks(experts, d, T):
+    # 17 to 32 tokens: one launch up to 1024 columns and 32 experts, a wave
+    # taking a token of each block (whole and partial second blocks)
+    check(experts, 3, experts, d, T)
+
+
 def test_more_blocks_than_plan_workgroups():
     # 67 x 1024 pairs: the plan kernel's 64 workgroups take more than one pair a thread
     check(16, 16, 16, 64, 4300)
