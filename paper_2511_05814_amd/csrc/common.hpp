@@ -175,12 +175,14 @@ struct PlanArgs {
   int T, K, E, S, layer, policy;
   int aging;  // aged LFU: lookup-clock ticks per halving of a count
   // Batches planned on the device (a slot for every expert): the kernel also
-  // writes the GEMM tiles; nullptr otherwise.  Small batches (ntiles ==
-  // nullptr) take one small-M tile per expert.  Others take two lists ordered
-  // (expert, column block, row block): the up list at tiles[0 ..], the down
-  // list at tiles[dn.first ..], their lengths written to ntiles[0] and [1].
+  // writes the GEMM tiles; nullptr otherwise.  Small-M launches take one tile
+  // per expert, at tiles[0 ..] (when small).  Others (when ntiles is not
+  // nullptr) take lists ordered (expert, column block, row block) at
+  // tiles[up.first ..] and tiles[dn.first ..], their lengths written to
+  // ntiles[0] and [1]; a list that no launch reads has cb == 0.
   GemmTile *tiles;
   int32_t *ntiles;
+  int small;
   TileList up, dn;
   int cus;  // compute units the tiles are spread over
   const uint8_t *arena_layer;  // this layer's slots
@@ -248,12 +250,12 @@ hipError_t launch_prefill_up(const GemmTile *tiles, const int32_t *ntiles, int g
 hipError_t launch_prefill_down(const GemmTile *tiles, const int32_t *ntiles, int grid, bool wide, const uint16_t *act,
                                float *Y, int d, int d_ff, const Launch &l);
 constexpr int prefill_tile_cols(bool up, bool wide) { return (up ? 128 : 256) / (wide ? 1 : 2); }
-// Small-M grouped GEMMs: one tile per expert, each with at most kSkinnyRows
-// rows; a workgroup per (tile, 16 output features).
-constexpr int kSkinnyRows = 16;
-hipError_t launch_prefill_skinny_up(const GemmTile *tiles, int ntiles, const uint16_t *xn, const int32_t *perm_tok,
+// Small-M grouped GEMMs: one tile per expert, each with at most max_rows <=
+// kSkinnyRows rows; a workgroup per (tile, 16 output features).
+constexpr int kSkinnyRows = 32;
+hipError_t launch_prefill_skinny_up(const GemmTile *tiles, int ntiles, int max_rows, const uint16_t *xn, const int32_t *perm_tok,
                                     uint16_t *act, int d, int d_ff, const Launch &l);
-hipError_t launch_prefill_skinny_down(const GemmTile *tiles, int ntiles, const uint16_t *act, float *Y, int d, int d_ff,
+hipError_t launch_prefill_skinny_down(const GemmTile *tiles, int ntiles, int max_rows, const uint16_t *act, float *Y, int d, int d_ff,
                                       const Launch &l);
 hipError_t launch_prefill_unpermute(float *H, const float *Y, const float *g, const int32_t *pos_of, int T,
                                     int d, int K, const Launch &l);

@@ -19,6 +19,7 @@
 #include "moe_offload.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -179,9 +180,10 @@ static PrefillLayout prefill_layout(int K, int d, int d_ff, int E, int S, int T,
     return at;
   };
   const size_t P = (size_t)T * K;
-  // every expert cut into the shortest row blocks and the narrowest columns
+  // every expert cut into the shortest row blocks and the narrowest columns,
+  // and a small-M tile of each
   const int up_cols = prefill_tile_cols(true, false), dn_cols = prefill_tile_cols(false, false);
-  p.tile_cap = (int)((P + 31) / 32 + E) * ((d_ff + up_cols - 1) / up_cols + (d + dn_cols - 1) / dn_cols);
+  p.tile_cap = (int)((P + 31) / 32 + E) * ((d_ff + up_cols - 1) / up_cols + (d + dn_cols - 1) / dn_cols) + E;
   int half = (E - S + 1) / 2;
   half = half < 1 ? 1 : (half > 4 ? 4 : half);
   p.ring = 2 * half;
@@ -926,6 +928,29 @@ static TileList tile_list(bool up, int ncols, long pairs, int experts, int cus, 
   return t;
 }
 
+// Does a grouped GEMM over `experts` experts (about) with `pairs` rows between
+// them, at most `most` each, take the small-M kernels?  With at most 16 rows
+// an expert always.  With 17 to 32 where its tiles (all of one row block) would
+// fill the chip badly: too few of them (a tile streams its weights at about 40
+// GB/s whatever else runs), or, of long weight rows, a second round that is
+// mostly empty.  Where long rows have most of two 16-row blocks a tile is
+// worth more.  us, tiles / small-M, weights from HBM:
+//   4 experts of 1024 x 1024, 17 tokens of top-1: up (64 tiles) 10.5 / 6.7, down (32) 9.3 / 4.8
+//   8 of 2048 x 2048, 32 of top-2: up (256) 31.5 / 28.6, down (128) 18.3 / 15.9
+//   8 of 2048 x 5632, 17 of top-2: up (349 wide) 82.4 / 63.1, down (127) 43.1 / 38.0
+//   64 of 2048 x 2048, 32 of top-2: up (653 wide) 122 / 99, down (327 wide) 68.7 / 50.5
+//   1 of 4096 x 14336, 32 of top-1: up (224) 48.0 / 75.6, down (32) 97.1 / 50.0
+//   4 of 4096 x 4096, 32 of top-2 (16 rows each): up (256) 57.4 / 62.2, down (128) 33.6 / 38.0
+//   16 of 2048 x 1408, 17 of top-4: up (349) 39.8 / 35.3, down (254) 15.9 / 25.1
+//   64 of 2048 x 1408, 32 of top-8: up (694 wide) 109 / 122, down (505 wide) 57.2 / 88.8
+//   8 of 4096 x 14336, 32 of top-2: up (896 wide) 313 / 344, down (256) 157 / 193
+static bool small_m(const TileList &t, bool wide, int depth, double experts, double pairs, int most, int cus) {
+  if (most <= 16) return true;
+  if (most > kSkinnyRows) return false;
+  const double tiles = t.cb * experts, few = wide ? 0.5 : depth >= 4000 && pairs >= 14.0 * experts ? 0.4 : 0.625;
+  return tiles < few * cus || (wide && depth >= 2000 && tiles > 1.05 * cus && tiles < 1.7 * cus);
+}
+
 // Batched prefill of one layer.  Routing and the cache decision run on the
 // device; the host then waits for the plan (a few hundred bytes), because it
 // has to issue one copy per streamed expert and size the grouped GEMMs:
@@ -937,8 +962,8 @@ static TileList tile_list(bool up, int ncols, long pairs, int experts, int cus, 
 //   copy:    newcomers nobody routed (wait A) -> event F; compute waits F
 //   compute: unpermute (h += sum_r g Y)
 // With a slot for every expert nothing is streamed, and the plan kernel also
-// plans the GEMMs (one small-M tile per expert for small batches, two tile
-// lists for others), so the host waits for nothing.
+// plans the GEMMs (a small-M tile per expert, a tile list for each other
+// launch), so the host waits for nothing.
 int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   const PrefillLayout &p = c->play;
   uint8_t *base = c->prefill_ws;
@@ -995,24 +1020,33 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   pa.policy = c->policy;
   pa.aging = c->policy == MOE_POLICY_LFU_AGED ? c->desc.aging_ticks : 0;
   // With a slot for every expert nothing is ever streamed: the plan kernel
-  // writes the GEMM tiles itself and the host does not wait for it.  Batches
-  // of at most kSkinnyRows tokens take the small-M GEMMs (every expert's rows
-  // fit them), others two tile lists whose lengths the GEMMs read on the
-  // device; the grids cover the longest lists any routing can give.
-  const bool on_device = c->S == c->E, skinny_plan = on_device && T <= kSkinnyRows;
+  // writes the GEMM tiles itself and the host does not wait for it.  Small-M
+  // launches take a tile per expert, others a tile list whose length the GEMM
+  // reads on the device; its grid covers the longest list any routing can give.
+  const bool on_device = c->S == c->E;
   const int cus = device_cus(c);
   const long pairs = (long)T * c->K;
   int32_t *dev_ntiles = reinterpret_cast<int32_t *>(base + p.ntiles);
-  bool up_wide = true, dn_wide = true;
-  pa.tiles = on_device ? tiles : nullptr;
-  pa.ntiles = on_device && !skinny_plan ? dev_ntiles : nullptr;
-  pa.up = tile_list(true, c->dff, pairs, c->E, cus, &up_wide);
-  pa.dn = tile_list(false, c->d, pairs, c->E, cus, &dn_wide);
-  pa.dn.first = pa.up.cap;
-  pa.cus = cus;
-  if (pa.ntiles && pa.up.cap + pa.dn.cap > p.tile_cap) {  // cannot happen: the capacity counts the shortest, narrowest tiles
-    c->sticky = MOE_ERR_HIP;
-    return fail(MOE_ERR_HIP, "prefill tile schedule overflow (capacity %d)", p.tile_cap);
+  bool up_wide = true, dn_wide = true, up_small = false, dn_small = false;
+  if (on_device) {
+    pa.tiles = tiles;
+    pa.up = tile_list(true, c->dff, pairs, c->E, cus, &up_wide);
+    pa.dn = tile_list(false, c->d, pairs, c->E, cus, &dn_wide);
+    // experts that T tokens reach, routed evenly
+    const double reached = c->E * (1.0 - std::pow(1.0 - (double)c->K / c->E, T));
+    up_small = small_m(pa.up, up_wide, c->d, reached, (double)pairs, T, cus);
+    dn_small = small_m(pa.dn, dn_wide, c->dff, reached, (double)pairs, T, cus);
+    pa.small = up_small || dn_small;
+    if (up_small) pa.up.cb = pa.up.cap = 0;
+    if (dn_small) pa.dn.cb = pa.dn.cap = 0;
+    pa.ntiles = up_small && dn_small ? nullptr : dev_ntiles;
+    pa.up.first = pa.small ? c->E : 0;
+    pa.dn.first = pa.up.first + pa.up.cap;
+    pa.cus = cus;
+    if (pa.dn.first + pa.dn.cap > p.tile_cap) {  // cannot happen: the capacity counts the shortest, narrowest tiles
+      c->sticky = MOE_ERR_HIP;
+      return fail(MOE_ERR_HIP, "prefill tile schedule overflow (capacity %d)", p.tile_cap);
+    }
   }
   pa.arena_layer = arena + (size_t)layer * c->S * c->B;
   pa.slot_bytes = c->B;
@@ -1022,14 +1056,14 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
     const double rows = (double)pairs;
     Launch lu, ld;
     HIP_TRY(c, kernel_span(c, c->cs, &lu, SPAN_GEMM_UP));
-    if (skinny_plan)
-      HIP_TRY(c, launch_prefill_skinny_up(tiles, c->E, xn, perm, act, c->d, c->dff, lu));
+    if (up_small)
+      HIP_TRY(c, launch_prefill_skinny_up(tiles, c->E, T, xn, perm, act, c->d, c->dff, lu));
     else
-      HIP_TRY(c, launch_prefill_up(tiles, dev_ntiles, pa.up.cap, up_wide, xn, perm, act, c->d, c->dff, lu));
+      HIP_TRY(c, launch_prefill_up(tiles + pa.up.first, dev_ntiles, pa.up.cap, up_wide, xn, perm, act, c->d, c->dff, lu));
     kernel_span_done(c, SPAN_GEMM_UP, lu, rows * 4.0 * c->d * c->dff);
     HIP_TRY(c, kernel_span(c, c->cs, &ld, SPAN_GEMM_DOWN));
-    if (skinny_plan)
-      HIP_TRY(c, launch_prefill_skinny_down(tiles, c->E, act, Y, c->d, c->dff, ld));
+    if (dn_small)
+      HIP_TRY(c, launch_prefill_skinny_down(tiles, c->E, T, act, Y, c->d, c->dff, ld));
     else
       HIP_TRY(c, launch_prefill_down(tiles + pa.dn.first, dev_ntiles + 1, pa.dn.cap, dn_wide, act, Y, c->d, c->dff, ld));
     kernel_span_done(c, SPAN_GEMM_DOWN, ld, rows * 2.0 * c->d * c->dff);
@@ -1107,9 +1141,7 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
     else
       ht[nt++] = GemmTile{weights[e], pl[e].off + m0, rows, n0, rows == pl[e].n};
   };
-  auto add_tiles = [&](const std::vector<int> &group, long rows, bool up, int &first, int &count, bool &wide) {
-    const int ncols = up ? c->dff : c->d;
-    const TileList tl = tile_list(up, ncols, rows, (int)group.size(), cus, &wide);
+  auto add_tiles = [&](const std::vector<int> &group, const TileList &tl) {
     int best = tl.hi;
     float best_cost = 0.0f;
     for (int r = tl.hi; r >= tl.lo; r -= 32) {
@@ -1125,38 +1157,48 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
         best_cost = cost;
       }
     }
-    first = nt;
     for (int e : group) {
       const int per = tile_rows(pl[e].n, best);
-      for (int n0 = 0; n0 < ncols; n0 += tl.cols)
+      for (int n0 = 0; n0 < tl.cb * tl.cols; n0 += tl.cols)
         for (int m0 = 0; m0 < pl[e].n; m0 += per) add_tile(e, m0, std::min(per, pl[e].n - m0), n0);
     }
-    count = nt - first;
+  };
+  // a group's launches: their tiles, the most rows one of its experts has, and
+  // the kernels they take
+  struct GroupGemm {
+    int first = 0, n = 0;
+    bool small = false, wide = true;
+  };
+  struct Group {
+    GroupGemm up, dn;
+    int most = 0;
+    long rows = 0;
   };
   const size_t ngroups = batches.size() + 1;
-  std::vector<int> up_first(ngroups), up_n(ngroups), dn_first(ngroups), dn_n(ngroups);
-  struct GroupKind {
-    bool skinny = false, up_wide = true, dn_wide = true;
-  };
-  std::vector<GroupKind> kind(ngroups);
-  std::vector<double> group_rows(ngroups, 0.0);
-  // a group whose experts all have few rows (batched decode) goes to the
-  // small-M kernels: one tile per expert, shared by the up and down launches
+  std::vector<Group> groups(ngroups);
+  // small-M launches take one tile per expert, which both may share
   auto add_group = [&](const std::vector<int> &group, size_t gi) {
-    int most = 0;
+    Group &gr = groups[gi];
+    if (group.empty()) return;
     for (int e : group) {
-      most = std::max(most, pl[e].n);
-      group_rows[gi] += pl[e].n;
+      gr.most = std::max(gr.most, pl[e].n);
+      gr.rows += pl[e].n;
     }
-    if (most <= kSkinnyRows) {
-      kind[gi].skinny = true;
-      up_first[gi] = dn_first[gi] = nt;
+    const int n = (int)group.size();
+    const TileList ul = tile_list(true, c->dff, gr.rows, n, cus, &gr.up.wide);
+    const TileList dl = tile_list(false, c->d, gr.rows, n, cus, &gr.dn.wide);
+    gr.up.small = small_m(ul, gr.up.wide, c->d, n, (double)gr.rows, gr.most, cus);
+    gr.dn.small = small_m(dl, gr.dn.wide, c->dff, n, (double)gr.rows, gr.most, cus);
+    const int small_first = nt;
+    if (gr.up.small || gr.dn.small)
       for (int e : group) add_tile(e, 0, pl[e].n, 0);
-      up_n[gi] = dn_n[gi] = nt - up_first[gi];
-    } else {
-      add_tiles(group, (long)group_rows[gi], true, up_first[gi], up_n[gi], kind[gi].up_wide);
-      add_tiles(group, (long)group_rows[gi], false, dn_first[gi], dn_n[gi], kind[gi].dn_wide);
-    }
+    auto fill = [&](GroupGemm &g, const TileList &tl) {
+      g.first = g.small ? small_first : nt;
+      if (!g.small) add_tiles(group, tl);
+      g.n = g.small ? n : nt - g.first;
+    };
+    fill(gr.up, ul);
+    fill(gr.dn, dl);
   };
   add_group(resident, 0);
   for (size_t bi = 0; bi < batches.size(); ++bi) add_group(batches[bi], bi + 1);
@@ -1220,20 +1262,22 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
 
   const double up_flop_per_row = 4.0 * c->d * c->dff, down_flop_per_row = 2.0 * c->d * c->dff;
   auto run_group = [&](size_t gi) -> int {
-    if (up_n[gi] <= 0) return MOE_OK;
+    const Group &gr = groups[gi];
+    if (gr.up.n <= 0) return MOE_OK;
+    const GemmTile *ut = tiles + gr.up.first, *dt = tiles + gr.dn.first;
     Launch lu, ld;
     HIP_TRY(c, kernel_span(c, c->cs, &lu, SPAN_GEMM_UP));
-    if (kind[gi].skinny)
-      HIP_TRY(c, launch_prefill_skinny_up(tiles + up_first[gi], up_n[gi], xn, perm, act, c->d, c->dff, lu));
+    if (gr.up.small)
+      HIP_TRY(c, launch_prefill_skinny_up(ut, gr.up.n, gr.most, xn, perm, act, c->d, c->dff, lu));
     else
-      HIP_TRY(c, launch_prefill_up(tiles + up_first[gi], nullptr, up_n[gi], kind[gi].up_wide, xn, perm, act, c->d, c->dff, lu));
-    kernel_span_done(c, SPAN_GEMM_UP, lu, group_rows[gi] * up_flop_per_row);
+      HIP_TRY(c, launch_prefill_up(ut, nullptr, gr.up.n, gr.up.wide, xn, perm, act, c->d, c->dff, lu));
+    kernel_span_done(c, SPAN_GEMM_UP, lu, gr.rows * up_flop_per_row);
     HIP_TRY(c, kernel_span(c, c->cs, &ld, SPAN_GEMM_DOWN));
-    if (kind[gi].skinny)
-      HIP_TRY(c, launch_prefill_skinny_down(tiles + dn_first[gi], dn_n[gi], act, Y, c->d, c->dff, ld));
+    if (gr.dn.small)
+      HIP_TRY(c, launch_prefill_skinny_down(dt, gr.dn.n, gr.most, act, Y, c->d, c->dff, ld));
     else
-      HIP_TRY(c, launch_prefill_down(tiles + dn_first[gi], nullptr, dn_n[gi], kind[gi].dn_wide, act, Y, c->d, c->dff, ld));
-    kernel_span_done(c, SPAN_GEMM_DOWN, ld, group_rows[gi] * down_flop_per_row);
+      HIP_TRY(c, launch_prefill_down(dt, nullptr, gr.dn.n, gr.dn.wide, act, Y, c->d, c->dff, ld));
+    kernel_span_done(c, SPAN_GEMM_DOWN, ld, gr.rows * down_flop_per_row);
     return MOE_OK;
   };
   hipEvent_t evA = c->pf_ev[0], evF = c->pf_ev[1];

@@ -19,14 +19,14 @@
 //              expert (into its new slot, or a staging ring) followed by the
 //              grouped GEMMs on those; the host schedules them from the plan,
 //              except with a slot for every expert, where the plan kernel
-//              writes the GEMM jobs and tiles itself
+//              writes the GEMM tiles itself
 //   4. unpermute  h_t += sum_r g_tr Y[pos(t, r)] in rank order (no atomics)
 //
 // The gate GEMM and the grouped GEMMs are dense contractions, so they run on
 // the matrix cores: the gate on the fp64 ones (exact products, fp64 sums),
 // the expert GEMMs (rows = pairs routed to one expert) on bf16 ones: tiles of
-// up to 256 rows (gemm.hip), or the small-M kernel here for groups of at most
-// 16 rows.
+// up to 256 rows (gemm.hip), or the small-M kernel here for groups of few
+// rows.
 #include "common.hpp"
 #include "moe_offload.h"
 
@@ -494,7 +494,8 @@ __device__ __forceinline__ void plan_share(const PlanArgs &a, int g, int G, cons
           GemmTile{tw[lo], offs[lo] + mb * per, min(per, cnt[lo] - mb * per), cb * (list == 0 ? a.up.cols : a.dn.cols),
                    nt == 1};
     }
-  } else if (a.tiles && keeper && in_range) {
+  }
+  if (a.tiles && a.small && keeper && in_range) {
     a.tiles[lane] = GemmTile{tw[lane], offs[lane], bad ? 0 : cnt[lane], 0, 1};
     if (bad) *a.err = ERR_BAD_LIST;
   }
@@ -655,19 +656,17 @@ __device__ __forceinline__ gemm_u32x4 buffer_load16(__amdgpu_buffer_rsrc_t r, ui
   return __builtin_bit_cast(gemm_u32x4, __builtin_amdgcn_raw_buffer_load_b128(r, byte_off, 0, 0));
 }
 
-// Small-M grouped GEMM: launches whose experts have at most kSkinnyRows rows
-// (batched decode).  A workgroup owns 16 output features of one expert for all
-// of its rows (one 16-row MFMA block).  Its four
-// waves split K in four; each streams its quarter of the 16 weight rows (of W1
-// and W3 in the up projection) from global memory straight into
-// v_mfma_f32_16x16x32_bf16 fragments, several 32-deep steps ahead, with
-// the rows' activations read alongside (from L2: every workgroup of the expert
-// reads them).  A row or feature past the end reads a valid row instead (its
-// outputs are not written); only a K tail that is not a multiple of 32 is
-// zeroed.  The four partial products meet in LDS and are added in wave order.
-// Batches of more than 16 tokens take the tiled kernels: with a second row
-// block here 32 tokens of top-8 over 64 experts took 126 / 103 us (up / down)
-// and 32 tokens of top-2 over 8 experts 373 / 221, the tiles 126 / 66 and 329 / 174.
+// Small-M grouped GEMM: launches whose experts have few rows (batched decode;
+// which ones: small_m in the engine).  A workgroup owns 16 output features of
+// one expert for all of its rows: one 16-row MFMA block, or two where it has 17
+// to 32 rows.  Its four waves split K in four; each streams its quarter of the
+// 16 weight rows (of W1 and W3 in the up projection) from global memory
+// straight into v_mfma_f32_16x16x32_bf16 fragments, several 32-deep steps
+// ahead, with the rows' activations read alongside (from L2: every workgroup of
+// the expert reads them).  A row or feature past the end reads a valid row
+// instead (its outputs are not written); only a K tail that is not a multiple
+// of 32 is zeroed.  The four partial products meet in LDS and are added in wave
+// order.
 constexpr int kSkinnyAheadUp = 8, kSkinnyAheadDown = 8;  // steps in flight per wave
 
 __device__ __forceinline__ bf16x8 load_frag(const uint16_t *p) {
@@ -678,23 +677,23 @@ __device__ __forceinline__ bf16x8 load_frag(__amdgpu_buffer_rsrc_t r, uint32_t b
   return __builtin_bit_cast(bf16x8, buffer_load16(r, byte_off));
 }
 
-template <bool UP, int AHEAD>
-__global__ __launch_bounds__(256) void prefill_skinny_kernel(const GemmTile *tiles, const uint16_t *a_src,
-                                                             const int32_t *perm_tok, void *out, int d, int d_ff) {
+// One tile of at most 16 * RB rows by the 16 features of block fb.
+template <bool UP, int AHEAD, int RB>
+__device__ __forceinline__ void skinny_tile(const GemmTile &t, int fb, const uint16_t *a_src, const int32_t *perm_tok,
+                                            void *out, int d, int d_ff, floatx4 (*red)[UP ? 2 : 1][RB][kWave]) {
   constexpr int NB = UP ? 2 : 1;  // B matrices: W1 and W3, or W2
-  __shared__ floatx4 red[4][NB][kWave];
   const int K = UP ? d : d_ff;  // reduction length
   const int N = UP ? d_ff : d;  // output features
-  const int nfb = (N + 15) / 16;
-  const int ti = blockIdx.x / nfb, fb = blockIdx.x - ti * nfb;
-  const GemmTile t = tiles[ti];
   const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-  const int M = min(t.rows, kSkinnyRows);
-  if (M <= 0) return;              // an expert without rows
+  const int M = min(t.rows, 16 * RB);
   const int kg = (lane / 16) * 8;  // this lane's 8 elements of a 32-deep step
-  // A row (token of the expert) and B row (feature) of this lane, clamped
-  const int m = t.row + min(lane % 16, M - 1);
-  const uint16_t *ap = (UP ? a_src + (size_t)perm_tok[m] * d : a_src + (size_t)m * d_ff) + kg;
+  // A rows (tokens of the expert) and B row (feature) of this lane, clamped
+  const uint16_t *ap[RB];
+#pragma unroll
+  for (int x = 0; x < RB; ++x) {
+    const int m = t.row + min(16 * x + lane % 16, M - 1);
+    ap[x] = (UP ? a_src + (size_t)perm_tok[m] * d : a_src + (size_t)m * d_ff) + kg;
+  }
   // B rows: features fb * 16 .. + nf - 1 of each weight matrix, read with
   // buffer loads (the pointer comes from the tile list; flat loads would make
   // every wait drain all the loads in flight)
@@ -706,26 +705,32 @@ __global__ __launch_bounds__(256) void prefill_skinny_kernel(const GemmTile *til
                        (uint32_t)nf * K * 2);
   const uint32_t boff = ((uint32_t)min(lane % 16, nf - 1) * K + kg) * 2;
 
-  floatx4 c[NB];
+  floatx4 c[NB][RB];
 #pragma unroll
-  for (int b = 0; b < NB; ++b) c[b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int x = 0; x < RB; ++x) c[b][x] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
 
   // this wave's full 32-deep steps
   const int full = K / 32;
   const int q = (full + 3) / 4;
   const int s0 = min(wave * q, full), s1 = min(s0 + q, full);
   const int n = s1 - s0;
-  bf16x8 wa[AHEAD][NB], xa[AHEAD];
+  bf16x8 wa[AHEAD][NB], xa[AHEAD][RB];
   // no load is conditional, so the compiler can count the loads in flight
   auto load = [&](int slot, int step) {
     const int k = step * 32;
 #pragma unroll
     for (int b = 0; b < NB; ++b) wa[slot][b] = load_frag(brs[b], boff + 2 * k);
-    xa[slot] = load_frag(ap + k);
+#pragma unroll
+    for (int x = 0; x < RB; ++x) xa[slot][x] = load_frag(ap[x] + k);
   };
   auto mma = [&](int slot) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) c[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[slot], wa[slot][b], c[b], 0, 0, 0);
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int x = 0; x < RB; ++x)
+        c[b][x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[slot][x], wa[slot][b], c[b][x], 0, 0, 0);
   };
   // straight-line main loop: a step past the wave's last reloads that step
   // (in bounds, never used); the last steps, which load nothing, are peeled
@@ -755,34 +760,60 @@ __global__ __launch_bounds__(256) void prefill_skinny_kernel(const GemmTile *til
       const bf16x8 v = load_frag(brs[b], boff + 2 * k);
       wa[0][b] = in ? v : z;
     }
-    const bf16x8 x0 = load_frag(ap + k);
-    xa[0] = in ? x0 : z;
+#pragma unroll
+    for (int x = 0; x < RB; ++x) {
+      const bf16x8 v = load_frag(ap[x] + k);
+      xa[0][x] = in ? v : z;
+    }
     mma(0);
   }
 #pragma unroll
-  for (int b = 0; b < NB; ++b) red[wave][b][lane] = c[b];
+  for (int b = 0; b < NB; ++b)
+#pragma unroll
+    for (int x = 0; x < RB; ++x) red[wave][b][x][lane] = c[b][x];
   __syncthreads();
   if (wave == 0) {
-    floatx4 r[NB];
+    floatx4 r[NB][RB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      r[b] = red[0][b][lane];
+    for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int w = 1; w < 4; ++w) r[b] += red[w][b][lane];
-    }
+      for (int x = 0; x < RB; ++x) {
+        r[b][x] = red[0][b][x][lane];
+#pragma unroll
+        for (int w = 1; w < 4; ++w) r[b][x] += red[w][b][x][lane];
+      }
     const int n_out = fb * 16 + lane % 16;
     if (n_out < N) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int mo = (lane / 16) * 4 + i;
-        if (mo >= M) continue;
-        if (UP)
-          static_cast<uint16_t *>(out)[(size_t)(t.row + mo) * N + n_out] = f32_to_bf16_rne(silu(r[0][i]) * r[NB - 1][i]);
-        else
-          static_cast<float *>(out)[(size_t)(t.row + mo) * N + n_out] = r[0][i];
-      }
+      for (int x = 0; x < RB; ++x)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int mo = 16 * x + (lane / 16) * 4 + i;
+          if (mo >= M) continue;
+          if (UP)
+            static_cast<uint16_t *>(out)[(size_t)(t.row + mo) * N + n_out] =
+                f32_to_bf16_rne(silu(r[0][x][i]) * r[NB - 1][x][i]);
+          else
+            static_cast<float *>(out)[(size_t)(t.row + mo) * N + n_out] = r[0][x][i];
+        }
     }
   }
+}
+
+template <bool UP, int AHEAD, int RB>
+__global__ __launch_bounds__(256) void prefill_skinny_kernel(const GemmTile *tiles, const uint16_t *a_src,
+                                                             const int32_t *perm_tok, void *out, int d, int d_ff) {
+  constexpr int NB = UP ? 2 : 1;
+  __shared__ floatx4 red[4 * NB * RB * kWave];
+  const int N = UP ? d_ff : d;  // output features
+  const int nfb = (N + 15) / 16;
+  const int ti = blockIdx.x / nfb, fb = blockIdx.x - ti * nfb;
+  const GemmTile t = tiles[ti];
+  if (t.rows <= 0) return;  // an expert without rows
+  if (RB == 1 || t.rows <= 16)
+    skinny_tile<UP, AHEAD, 1>(t, fb, a_src, perm_tok, out, d, d_ff, reinterpret_cast<floatx4 (*)[NB][1][kWave]>(red));
+  else
+    skinny_tile<UP, AHEAD, RB>(t, fb, a_src, perm_tok, out, d, d_ff, reinterpret_cast<floatx4 (*)[NB][RB][kWave]>(red));
 }
 
 // ---------------------------------------------------------------------------
@@ -900,19 +931,25 @@ hipError_t launch_prefill_route_plan(const PrefillArgs &a, const PlanArgs &p, co
   return hipGetLastError();
 }
 
-hipError_t launch_prefill_skinny_up(const GemmTile *tiles, int ntiles, const uint16_t *xn, const int32_t *perm_tok,
-                                    uint16_t *act, int d, int d_ff, const Launch &l) {
+hipError_t launch_prefill_skinny_up(const GemmTile *tiles, int ntiles, int max_rows, const uint16_t *xn,
+                                    const int32_t *perm_tok, uint16_t *act, int d, int d_ff, const Launch &l) {
   if (ntiles <= 0) return hipSuccess;
-  MOE_LAUNCH((prefill_skinny_kernel<true, kSkinnyAheadUp>), dim3(ntiles * ((d_ff + 15) / 16)), dim3(256), 0, l, tiles, xn,
-             perm_tok, (void *)act, d, d_ff);
+  const dim3 grid(ntiles * ((d_ff + 15) / 16));
+  if (max_rows > 16)
+    MOE_LAUNCH((prefill_skinny_kernel<true, kSkinnyAheadUp, 2>), grid, dim3(256), 0, l, tiles, xn, perm_tok, (void *)act, d, d_ff);
+  else
+    MOE_LAUNCH((prefill_skinny_kernel<true, kSkinnyAheadUp, 1>), grid, dim3(256), 0, l, tiles, xn, perm_tok, (void *)act, d, d_ff);
   return hipGetLastError();
 }
 
-hipError_t launch_prefill_skinny_down(const GemmTile *tiles, int ntiles, const uint16_t *act, float *Y, int d, int d_ff,
-                                      const Launch &l) {
+hipError_t launch_prefill_skinny_down(const GemmTile *tiles, int ntiles, int max_rows, const uint16_t *act, float *Y, int d,
+                                      int d_ff, const Launch &l) {
   if (ntiles <= 0) return hipSuccess;
-  MOE_LAUNCH((prefill_skinny_kernel<false, kSkinnyAheadDown>), dim3(ntiles * ((d + 15) / 16)), dim3(256), 0, l, tiles, act,
-             nullptr, (void *)Y, d, d_ff);
+  const dim3 grid(ntiles * ((d + 15) / 16));
+  if (max_rows > 16)
+    MOE_LAUNCH((prefill_skinny_kernel<false, kSkinnyAheadDown, 2>), grid, dim3(256), 0, l, tiles, act, nullptr, (void *)Y, d, d_ff);
+  else
+    MOE_LAUNCH((prefill_skinny_kernel<false, kSkinnyAheadDown, 1>), grid, dim3(256), 0, l, tiles, act, nullptr, (void *)Y, d, d_ff);
   return hipGetLastError();
 }
 

@@ -48,8 +48,53 @@ def test_down_tile_heights():
 def test_small_and_ragged_tiles(d, d_ff):
     # one to five slices (fewer than the ring holds, with and without a K
     # tail), partial column blocks, narrow tiles (at most 48 rows an expert)
-    # and, from 49 rows on, wide ones
+    # and, from 49 rows on, wide ones; 17 and 31 rows take the small-M kernels
     check(d, d_ff, 3, [17, 31, 48, 49, 100])
+
+
+@pytest.mark.parametrize("d,d_ff", [(48, 200), (64, 64), (136, 192), (192, 136), (320, 264)])
+def test_tiles_of_few_rows(d, d_ff):
+    # more than 32 tokens, so tiles, but one expert a token of 4: tiles of one
+    # row block over one to five slices.  (Rounding x and act to bf16 alone,
+    # in fp64 arithmetic, puts the worst of these rows off by 4.4e-3 at 48 by
+    # 200, but by 6.2e-3 at 40 by 72, above the bound of 6e-3: the errors of few
+    # columns do not average.)
+    cfg = wl.CONFIGS["tiny-stack"].with_(layers=1, experts=4, top_k=1, d_model=d, d_ff=d_ff, dtype="bf16", tokens=1,
+                                         prefill_tokens=40)
+    _say("tiles of few rows", d, d_ff)
+    rig = Rig(cfg)
+    moe = rig.cache(4, "lfu", max_prefill_tokens=40)
+    prefill_and_check(rig, moe, "lfu", 4, 40, list(range(0, 40, 3)))
+    moe.close()
+    rig.store.close()
+
+
+@pytest.mark.parametrize("T", [16, 17, 31, 32])
+@pytest.mark.parametrize("d,d_ff", [(40, 200), (136, 72), (264, 520)])
+def test_small_m_row_blocks(d, d_ff, T):
+    # too few tiles for the chip, so the small-M kernels: one full 16-row block
+    # and two, each with a K tail
+    check(d, d_ff, 3, [T])
+
+
+@pytest.mark.parametrize("d,d_ff", [(520, 4104), (4104, 520)])
+def test_one_launch_of_tiles_one_of_small_m(d, d_ff):
+    # 4 experts: 260 narrow tiles one way and 20 the other
+    check(d, d_ff, 4, [17, 32])
+
+
+@pytest.mark.parametrize("T", [20, 32, 40])
+@pytest.mark.parametrize("slots", [2, 5])
+def test_host_planned_small_m(T, slots):
+    # groups whose experts have a few to some 30 rows, resident and streamed
+    cfg = wl.CONFIGS["tiny-stack"].with_(layers=1, experts=6, top_k=2, d_model=136, d_ff=200, dtype="bf16", tokens=1,
+                                         prefill_tokens=T)
+    _say("host-planned small-M", T, slots)
+    rig = Rig(cfg)
+    moe = rig.cache(slots, "lfu", max_prefill_tokens=T)
+    prefill_and_check(rig, moe, "lfu", slots, T, list(range(T)))
+    moe.close()
+    rig.store.close()
 
 
 @pytest.mark.parametrize("T", [300, 384])

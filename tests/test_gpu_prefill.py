@@ -164,7 +164,7 @@ def test_small_prefill_fine_grained(T):
 @pytest.mark.parametrize("T", [1, 13, 32])
 def test_device_planned_batches(T):
     # a slot for every expert and at most 32 tokens: the plan kernel writes the
-    # GEMM jobs and the host does not read the plan back; ragged d and d_ff
+    # GEMM tiles and the host does not read the plan back; ragged d and d_ff
     # (K tails of the small-M GEMMs), 5 experts, top-3 (32 tokens can give an
     # expert 32 rows: two 16-row MFMA blocks)
     cfg = wl.CONFIGS["tiny-stack"].with_(layers=2, experts=5, top_k=3, d_model=136, d_ff=200,
@@ -182,7 +182,7 @@ def test_prefill_largest_top_k(slots, T):
     # top-16 over 64 experts, so the un-permute adds each token's ranks in two
     # batches of eight: with 16 slots the batch streams experts (planned on the
     # host), with a slot for every expert and 32 tokens it is planned on the
-    # device (small-M tiles, up to 32 rows an expert)
+    # device (tiles up, small-M down)
     cfg = wl.CONFIGS["tiny-stack"].with_(layers=2, experts=64, top_k=16, d_model=128, d_ff=256,
                                          dtype="bf16", tokens=2, prefill_tokens=T)
     _say("prefill top-16", slots, T)
