@@ -257,7 +257,7 @@ struct moe_cache {
   // batched prefill
   PrefillLayout play;
   PrefillPlan *h_plan = nullptr;   // pinned: plan of the last prefill layer
-  uint8_t *h_sched = nullptr;      // pinned: GEMM tiles uploaded per layer
+  uint8_t *h_sched = nullptr;      // pinned: GEMM tiles uploaded per layer (batches planned on the host)
   std::vector<hipEvent_t> pf_ev;   // prefill ordering events
   // kernel timing (moe_cache_set_timing)
   int timing = MOE_TIMING_OFF;
@@ -584,9 +584,10 @@ int moe_cache_bind(moe_cache_t *c, const moe_model_desc *d) {
     // the plan of every expert, then the device's error word
     HIP_TRY0(pool_pinned(c->dev, sizeof(PrefillPlan) * kMaxE + sizeof(int32_t), reinterpret_cast<void **>(&c->h_plan),
                          &c->plan_bytes));
-    HIP_TRY0(pool_pinned(c->dev,
-                         sizeof(GemmTile) * (size_t)c->play.tile_cap + sizeof(FetchList) * kPrefillLists,
-                         reinterpret_cast<void **>(&c->h_sched), &c->sched_bytes));
+    // with a slot for every expert the device plans every batch: nothing is uploaded
+    if (c->S < c->E)
+      HIP_TRY0(pool_pinned(c->dev, sizeof(GemmTile) * (size_t)c->play.tile_cap + sizeof(FetchList) * kPrefillLists,
+                           reinterpret_cast<void **>(&c->h_sched), &c->sched_bytes));
     c->pf_ev.assign(2 * kMaxE + 4, nullptr);
     for (auto &e : c->pf_ev) HIP_TRY0(pool_event(c->dev, false, &e));
   }
