@@ -59,10 +59,14 @@ __device__ __forceinline__ uint32_t bf16_rne(float f) {
   return u >> 16;
 }
 
-// v / (1 + e^-v) with the hardware's exponential and reciprocal (one ulp
-// each); the result is rounded to bf16.
+// v / (1 + e^-v).  The quotient is v times the hardware's reciprocal (one ulp)
+// with one step of refinement, which rounds as the division does but for one
+// quotient in some 2^22; div_fixup sets the infinite and NaN cases.  4096 tokens
+// of top-8 over 64 experts: 718 us a pass with the reciprocal alone, 720 so, 728
+// with the compiler's division.
 __device__ __forceinline__ float silu(float v) {
-  return v * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(v * -1.44269504088896340736f));
+  const float x = 1.0f + __expf(-v), r = __builtin_amdgcn_rcpf(x), q = v * r;
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-x, q, v), r, q), x, v);
 }
 
 // One wave-wide 16-byte-a-lane load into LDS at m0 + 16 * lane.  Written as
