@@ -313,6 +313,9 @@ __global__ __launch_bounds__(kFusedThreads) void ffn_down_wide_kernel(FfnArgs a,
   const int row0 = blockIdx.x * rows, nrows = min(rows, d - row0);
   __shared__ float dots[W][kWideRowsMax];
   if (lane < nrows) dots[wave][lane] = 0.0f;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // lane 63 adds to what other lanes set
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   const int K = min(a.K, a.route->k);
   for (int u = wave; u < K * cpr; u += W) {
     const int rank = u / cpr, c0 = (u - rank * cpr) * CH;

@@ -62,8 +62,8 @@ __device__ __forceinline__ uint32_t bf16_rne(float f) {
 // v / (1 + e^-v).  The quotient is v times the hardware's reciprocal (one ulp)
 // with one step of refinement, which rounds as the division does but for one
 // quotient in some 2^22; div_fixup sets the infinite and NaN cases.  4096 tokens
-// of top-8 over 64 experts: 718 us a pass with the reciprocal alone, 720 so, 728
-// with the compiler's division.
+// of top-8 over 64 experts: 720 us a pass with the reciprocal alone and so; the
+// compiler's division took 1.5% more.
 __device__ __forceinline__ float silu(float v) {
   const float x = 1.0f + __expf(-v), r = __builtin_amdgcn_rcpf(x), q = v * r;
   return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-x, q, v), r, q), x, v);
@@ -73,8 +73,9 @@ __device__ __forceinline__ float silu(float v) {
 // instructions of their own rather than the compiler's builtin: the compiler
 // tracks loads in flight into LDS per array, loses track across a ring's loop
 // and then waits for all of them before reading any slice; here the kernel's
-// own waits (wait_vm) are the only ones.  M0 carries the LDS address; the
-// compiler sets M0 itself before any instruction of its own that reads it
+// own waits (wait_vm) are the only ones.  M0 carries the LDS address.  It is a
+// reserved register, which a clobber list cannot name: the compiler keeps
+// nothing in it and sets it before any instruction of its own that reads it
 // (none in this kernel: gfx9 LDS instructions do not use it).
 // ONCE: non-temporal.
 template <bool ONCE>
@@ -138,7 +139,10 @@ __device__ __forceinline__ void gemm_tile(const GemmTile &t, const uint16_t *a_s
 
   // sources: load instruction i of the wave fills slice rows 8 (4 i + wave) ..
   // + 7.  Rows past the tile's end read its last row and columns past N the
-  // last one (their results are not written).
+  // last one (their results are not written).  perm_tok names a token of the
+  // batch at every position below its pair count: the plan writes them all, from
+  // ids and counts that the route kernel takes from one register (a clamp here
+  // costs 1%: 4096 tokens of top-8 over 64 experts 720 -> 728 us).
   const int lr = lane / 8, lc = (lane & 7) ^ ((4 * (wave & 1) + lane / 16) & 7);
   const uint8_t *ap[IA];
 #pragma unroll
@@ -231,7 +235,7 @@ __device__ __forceinline__ void gemm_tile(const GemmTile &t, const uint16_t *a_s
     c[m / YW][m % YW] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.b[m % YW], F.a[m / YW], c[m / YW][m % YW], 0, 0, 0);  \
     __builtin_amdgcn_sched_barrier(0);                                                                   \
     _Pragma("unroll") for (int q = 0; q < (COUNT); ++q)                                                  \
-      if (q * M2 / (COUNT) == m) {                                                                       \
+      if (q * M2 / max((COUNT), 1) == m) {                                                               \
         LOAD;                                                                                            \
         __builtin_amdgcn_sched_barrier(0);                                                               \
       }                                                                                                  \
