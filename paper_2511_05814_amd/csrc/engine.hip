@@ -919,6 +919,7 @@ static TileList tile_list(bool up, int ncols, long pairs, int experts, int cus, 
   t.cols = prefill_tile_cols(up, *wide);
   t.cb = (ncols + t.cols - 1) / t.cols;
   t.hi = *wide ? kWideRows : kNarrowRows;
+  t.slots = *wide ? cus : 2 * cus;
   // tiles of at most r rows: an expert with n > 0 rows has at most
   // 1 + (n - 1) / r of them per column block
   const long m = std::min<long>(experts, pairs);
@@ -1043,7 +1044,6 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
     pa.ntiles = up_small && dn_small ? nullptr : dev_ntiles;
     pa.up.first = pa.small ? c->E : 0;
     pa.dn.first = pa.up.first + pa.up.cap;
-    pa.cus = cus;
     if (pa.dn.first + pa.dn.cap > p.tile_cap) {  // cannot happen: the capacity counts the shortest, narrowest tiles
       c->sticky = MOE_ERR_HIP;
       return fail(MOE_ERR_HIP, "prefill tile schedule overflow (capacity %d)", p.tile_cap);
@@ -1146,13 +1146,13 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
     int best = tl.hi;
     float best_cost = 0.0f;
     for (int r = tl.hi; r >= tl.lo; r -= 32) {
-      long n = 0, blocks = 0;
+      int n = 0, blocks = 0;
       for (int e : group) {
         const int per = tile_rows(pl[e].n, r), k = (pl[e].n + per - 1) / per;
         n += k;
-        blocks += (long)k * (per / 32);
+        blocks += k * (per / 32);
       }
-      const float cost = tile_cost((int)(tl.cb * n), (int)(tl.cb * blocks), cus);
+      const float cost = tile_cost(tl, n, blocks);
       if (r == tl.hi || cost < best_cost) {
         best = r;
         best_cost = cost;

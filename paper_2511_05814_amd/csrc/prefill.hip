@@ -442,7 +442,7 @@ __device__ __forceinline__ void plan_share(const PlanArgs &a, int g, int G, cons
       if (lane < 2) {
         const TileList &tl = lane == 0 ? a.up : a.dn;
         const int r = 32 * wave;
-        tcost[lane][wave - 1] = r >= tl.lo && r <= tl.hi ? tile_cost(tl.cb * nt, tl.cb * blocks, a.cus) : __builtin_inff();
+        tcost[lane][wave - 1] = r >= tl.lo && r <= tl.hi ? tile_cost(tl, nt, blocks) : __builtin_inff();
       }
     }
     __syncthreads();
