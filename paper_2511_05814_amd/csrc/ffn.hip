@@ -340,12 +340,16 @@ __global__ __launch_bounds__(kFusedThreads) void ffn_down_wide_kernel(FfnArgs a,
         if (lane == kWave - 1 && r + q < nrows) dots[wave][r + q] += v;
       }
     };
+    if (nrows <= RPW) {  // nothing to refill: a refill past the last row would read it again
+      use(wa, 0);
+      continue;
+    }
     for (int r = 0; r < nrows; r += 2 * RPW) {
       load(wb, r + RPW);
       __builtin_amdgcn_sched_barrier(0);
       use(wa, r);
       __builtin_amdgcn_sched_barrier(0);
-      load(wa, r + 2 * RPW);
+      if (r + 2 * RPW < nrows) load(wa, r + 2 * RPW);
       __builtin_amdgcn_sched_barrier(0);
       use(wb, r + RPW);
     }
@@ -509,17 +513,22 @@ void launch_down_fused(bool ragged, const FfnArgs &a, const Launch &l) {
 constexpr int kChunkSteps = 2;  // column steps per chunk of the chunked kernel
 
 // Does one down launch do the whole projection?  Narrow experts always.  Wide
-// ones when the launch reads at most 24 MiB: it is then bound by launches, and
-// the reduction's costs 2.6 us; above, many short (rank, chunk) workgroups
-// stream faster than long-lived waves do.  A decode step on bf16 experts, us
-// with the chunks and the reduction / in one launch: 2 of d 256, d_ff 4096 (4
-// MiB) 18.9 / 16.4; 2 of 1024 x 4096 (16 MiB) 19.2 / 16.4; 4 of 1024 x 4096 (32
-// MiB) 20.0 / 20.4; 4 of 512 x 14336 (56 MiB) 29.0 / 31.7; 2 of 4096 x 14336
-// (224 MiB) 100 / 103.
-constexpr long kDownInOneBytes = 24l << 20;
+// ones when the launch reads at most 64 MiB (24 MiB of fewer than 512 rows of h,
+// too few for a workgroup on every compute unit): the reduction's launch then
+// costs more than it gains; above, short (rank, chunk) workgroups stream as
+// fast as long-lived waves or faster.  A decode step through layers of 1.2 GB in
+// all, us with the chunks and the reduction / in one launch, K x d x d_ff:
+//   bf16  2 x 1024 x 4096 (16 MiB) 312 / 296, 8 x 512 x 3072 (24) 376 / 352,
+//         1 x 4096 x 4096 (32) 174 / 164, 4 x 2048 x 4096 (64) 211 / 202, 8 x 1024 x
+//         4096 (64) 260 / 263, 2 x 4096 x 8192 (128) 288 / 286, 8 x 2048 x 4096
+//         (128) 279 / 281, 2 x 4096 x 14336 (224) 454 / 457, 16 x 256 x 2560 (20)
+//         490 / 489, 16 x 256 x 4096 (32) 416 / 430
+//   fp32  2 x 1024 x 3072 (24) 254 / 233, 4 x 1024 x 2048 (32) 270 / 251, 8 x 512 x
+//         4096 (64) 280 / 247, 16 x 512 x 2048 (64) 280 / 255, 8 x 1024 x 4096
+//         (128) 292 / 279, 16 x 256 x 1536 (24) 393 / 389
 bool down_in_one(int K, int d, int d_ff, int dtype) {
   const int elem = dtype == 1 ? 2 : 4, step = kWave * (16 / elem);
-  return d_ff <= 4 * step || (long)K * d * d_ff * elem <= kDownInOneBytes;
+  return d_ff <= 4 * step || (long)K * d * d_ff * elem <= (d < 512 ? 24l : 64l) << 20;
 }
 
 template <int DT>
