@@ -160,13 +160,14 @@ hipError_t scratch_on_device(int dev, uint8_t **out) {
 namespace moe {
 // Prefill workspace for batches of up to T tokens (offsets from its base).
 struct PrefillLayout {
-  size_t ids = 0, g = 0, zpart = 0, blk_cnt = 0, blk_last = 0, xn = 0, perm = 0, pos = 0, plan = 0, tiles = 0, act = 0,
+  size_t ids = 0, g = 0, zpart = 0, blk_cnt = 0, blk_last = 0, xn = 0, perm = 0, pos = 0, tiles = 0, act = 0,
          y = 0, staging = 0, coded = 0, lists = 0, ntiles = 0, total = 0;
   int tile_cap = 0;  // GEMM tiles the schedule can hold
   int ring = 0;      // staging slots for experts streamed through the batch
 };
 // fetch lists one prefill layer can need with a coded host store
 constexpr int kPrefillLists = 2 * kMaxE + 2;
+constexpr size_t kErrBytes = 256;  // the error word and both trace counts
 
 // Bh > 0: a coded host store, whose experts are copied to `coded` (room for
 // half a ring) and rebuilt from there through device-side fetch lists.
@@ -198,7 +199,6 @@ static PrefillLayout prefill_layout(int K, int d, int d_ff, int E, int S, int T,
   p.xn = take((size_t)T * d * 2);
   p.perm = take(P * 4);
   p.pos = take(P * 4);
-  p.plan = take(sizeof(PrefillPlan) * kMaxE);
   p.tiles = take(sizeof(GemmTile) * (size_t)p.tile_cap);
   p.act = take(P * d_ff * 2);
   p.y = take(P * d * 4);
@@ -251,12 +251,12 @@ struct moe_cache {
   int dev = 0;                  // device the handle was bound on (owner of its pooled objects)
   uint8_t *scratch = nullptr;   // that device's static scratch (moe_decode_layer_noalloc)
   FetchList *mirror = nullptr;  // pinned host: demand list, prefetch list, error word (DMA / split modes)
-  size_t mirror_bytes = 0, plan_bytes = 0, sched_bytes = 0;  // sizes of the pooled pinned buffers
+  size_t mirror_bytes = 0, back_bytes = 0, sched_bytes = 0;  // sizes of the pooled pinned buffers
   int last_route_kind = 0;      // 0 none, 1 decode, 2 prefill
   int last_prefill_T = 0;
   // batched prefill
   PrefillLayout play;
-  PrefillPlan *h_plan = nullptr;   // pinned: plan of the last prefill layer
+  uint8_t *h_back = nullptr;       // pinned: error word and plan of the last prefill layer
   uint8_t *h_sched = nullptr;      // pinned: GEMM tiles uploaded per layer (batches planned on the host)
   std::vector<hipEvent_t> pf_ev;   // prefill ordering events
   // kernel timing (moe_cache_set_timing)
@@ -454,7 +454,8 @@ static Layout make_layout(const moe_cache *c, const moe_model_desc *d) {
   l.plists = take(sizeof(FetchList) * c->L);
   l.route = take(sizeof(RouteOut));
   l.hostptrs = take(sizeof(void *) * c->L);
-  l.err = take(256);
+  // the plan of a prefill layer stands right behind, so that the host reads both in one copy
+  l.err = take(kErrBytes + (d->max_prefill_tokens > 0 ? sizeof(PrefillPlan) * kMaxE : 0));
   l.act = take(sizeof(float) * d->top_k * (size_t)d->d_ff);
   l.part = take(sizeof(float) * (size_t)ffn_down_chunks(d->top_k, d->d_model, d->d_ff, d->dtype) * d->d_model);
   const uint64_t B = expert_bytes(d);
@@ -581,9 +582,8 @@ int moe_cache_bind(moe_cache_t *c, const moe_model_desc *d) {
   HIP_TRY0(pool_pinned(c->dev, 3 * sizeof(FetchList), reinterpret_cast<void **>(&c->mirror), &c->mirror_bytes));
   if (c->max_T > 0) {
     c->play = prefill_layout(c->K, c->d, c->dff, c->E, c->S, c->max_T, c->B, coded_store(c->host_format) ? c->Bh : 0);
-    // the plan of every expert, then the device's error word
-    HIP_TRY0(pool_pinned(c->dev, sizeof(PrefillPlan) * kMaxE + sizeof(int32_t), reinterpret_cast<void **>(&c->h_plan),
-                         &c->plan_bytes));
+    HIP_TRY0(pool_pinned(c->dev, kErrBytes + sizeof(PrefillPlan) * kMaxE, reinterpret_cast<void **>(&c->h_back),
+                         &c->back_bytes));
     // with a slot for every expert the device plans every batch: nothing is uploaded
     if (c->S < c->E)
       HIP_TRY0(pool_pinned(c->dev, sizeof(GemmTile) * (size_t)c->play.tile_cap + sizeof(FetchList) * kPrefillLists,
@@ -619,7 +619,7 @@ int moe_cache_reset(moe_cache_t *c) {
   HIP_TRY(c, hipMemsetAsync(c->ws + c->lay.dlists, 0, sizeof(FetchList) * c->L, c->cs));
   HIP_TRY(c, hipMemsetAsync(c->ws + c->lay.plists, 0, sizeof(FetchList) * c->L, c->cs));
   HIP_TRY(c, hipMemsetAsync(c->ws + c->lay.route, 0, sizeof(RouteOut), c->cs));
-  HIP_TRY(c, hipMemsetAsync(c->ws + c->lay.err, 0, 256, c->cs));  // error word and both trace counts
+  HIP_TRY(c, hipMemsetAsync(c->ws + c->lay.err, 0, kErrBytes, c->cs));  // error word and both trace counts
   c->tpar = 0;
   {
     // the copy kernel dereferences this table: check it survived
@@ -974,7 +974,7 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   uint16_t *xn = reinterpret_cast<uint16_t *>(base + p.xn);
   int32_t *perm = reinterpret_cast<int32_t *>(base + p.perm);
   int32_t *pos = reinterpret_cast<int32_t *>(base + p.pos);
-  PrefillPlan *plan = reinterpret_cast<PrefillPlan *>(base + p.plan);
+  PrefillPlan *plan = reinterpret_cast<PrefillPlan *>(reinterpret_cast<uint8_t *>(c->err) + kErrBytes);
   GemmTile *tiles = reinterpret_cast<GemmTile *>(base + p.tiles);
   uint16_t *act = reinterpret_cast<uint16_t *>(base + p.act);
   float *Y = reinterpret_cast<float *>(base + p.y);
@@ -1074,14 +1074,12 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
     c->last_prefill_T = T;
     return MOE_OK;  // routing errors surface at the next synchronising call
   }
-  // one wait for both the plan and the error word (a second, synchronous
-  // read of the word cost another round trip of about 30 us per layer)
-  int32_t *h_err = reinterpret_cast<int32_t *>(c->h_plan + kMaxE);
-  HIP_TRY(c, hipMemcpyAsync(c->h_plan, plan, sizeof(PrefillPlan) * c->E, hipMemcpyDeviceToHost, c->cs));
-  HIP_TRY(c, hipMemcpyAsync(h_err, c->err, sizeof(int32_t), hipMemcpyDeviceToHost, c->cs));
+  // one copy and one wait for both the error word and the plan (a copy each
+  // cost another 4 us a layer, a second wait about 30)
+  HIP_TRY(c, hipMemcpyAsync(c->h_back, c->err, kErrBytes + sizeof(PrefillPlan) * c->E, hipMemcpyDeviceToHost, c->cs));
   HIP_TRY(c, hipStreamSynchronize(c->cs));
   {
-    const int32_t e = *h_err;
+    const int32_t e = *reinterpret_cast<const int32_t *>(c->h_back);
     if (e != ERR_NONE) {
       c->sticky = MOE_ERR_HIP;
       return fail(MOE_ERR_HIP, "prefill routing produced an invalid expert id (code %d)", e);
@@ -1092,7 +1090,7 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
 
   // weights of every routed expert, where the GEMMs will find them
   const int E = c->E;
-  const PrefillPlan *pl = c->h_plan;
+  const PrefillPlan *pl = reinterpret_cast<const PrefillPlan *>(c->h_back + kErrBytes);
   const uint16_t *weights[kMaxE] = {};
   GemmTile *ht = reinterpret_cast<GemmTile *>(c->h_sched);
   std::vector<int> resident, streamed, unrouted_new;
@@ -1636,7 +1634,7 @@ void moe_cache_destroy(moe_cache_t *c) {
     sync_ev.insert(sync_ev.end(), c->pf_ev.begin(), c->pf_ev.end());
     sync_ev.push_back(c->ev_router);
     pool_give_back(c->dev, sync_ev, c->ev_pool, c->ms,
-                   {{c->mirror_bytes, c->mirror}, {c->plan_bytes, c->h_plan}, {c->sched_bytes, c->h_sched}});
+                   {{c->mirror_bytes, c->mirror}, {c->back_bytes, c->h_back}, {c->sched_bytes, c->h_sched}});
     (void)hipGetLastError();
   }
   delete c;
