@@ -513,22 +513,27 @@ void launch_down_fused(bool ragged, const FfnArgs &a, const Launch &l) {
 constexpr int kChunkSteps = 2;  // column steps per chunk of the chunked kernel
 
 // Does one down launch do the whole projection?  Narrow experts always.  Wide
-// ones when the launch reads at most 64 MiB (24 MiB of fewer than 512 rows of h,
-// too few for a workgroup on every compute unit): the reduction's launch then
-// costs more than it gains; above, short (rank, chunk) workgroups stream as
-// fast as long-lived waves or faster.  A decode step through layers of 1.2 GB in
-// all, us with the chunks and the reduction / in one launch, K x d x d_ff:
-//   bf16  2 x 1024 x 4096 (16 MiB) 312 / 296, 8 x 512 x 3072 (24) 376 / 352,
-//         1 x 4096 x 4096 (32) 174 / 164, 4 x 2048 x 4096 (64) 211 / 202, 8 x 1024 x
-//         4096 (64) 260 / 263, 2 x 4096 x 8192 (128) 288 / 286, 8 x 2048 x 4096
-//         (128) 279 / 281, 2 x 4096 x 14336 (224) 454 / 457, 16 x 256 x 2560 (20)
-//         490 / 489, 16 x 256 x 4096 (32) 416 / 430
-//   fp32  2 x 1024 x 3072 (24) 254 / 233, 4 x 1024 x 2048 (32) 270 / 251, 8 x 512 x
-//         4096 (64) 280 / 247, 16 x 512 x 2048 (64) 280 / 255, 8 x 1024 x 4096
-//         (128) 292 / 279, 16 x 256 x 1536 (24) 393 / 389
+// ones when the launch reads at most 24 MiB: the reduction's launch then costs
+// more than it gains.  Above, one launch is faster where the rows of h divide
+// into equal workgroups for all compute units and slower where they don't; the
+// chunks' many short workgroups even that out.  us with the chunks and the
+// reduction / in one launch, 16 tokens through a layer of 1.2 GB (or as many as
+// 64 experts make), K x d x d_ff:
+//   to 24 MiB, bf16  1 x 2048 x 4096 (16 MiB) 351 / 323, 2 x 1024 x 6144 (24) 407 / 383,
+//     4 x 328 x 3488 (9) 315 / 302, 5 x 520 x 2344 (12) 381 / 366, 8 x 512 x 3072 (24)
+//     415 / 391, 3 x 256 x 14336 (21) 449 / 464, 6 x 584 x 2744 (18) 415 / 435, 7 x
+//     392 x 4512 (24) 446 / 440
+//   to 24 MiB, fp32  1 x 4096 x 1288 (20) 545 / 524, 2 x 1024 x 3072 (24) 392 / 362, 8 x
+//     456 x 1080 (15) 355 / 326, 16 x 256 x 1536 (24) 414 / 412
+//   above, bf16  4 x 2048 x 4096 (64) 679 / 655, 8 x 1024 x 4096 (64) 720 / 720, 2 x 1096 x
+//     10304 (43) 637 / 676, 6 x 584 x 8048 (54) 702 / 775, 3 x 2312 x 3056 (40) 602 /
+//     631, 2 x 4096 x 14336 (224, layers of 1.2 GB in turn) 454 / 457
+//   above, fp32  8 x 512 x 4096 (64) 731 / 673, 3 x 1800 x 2088 (43) 599 / 560, 6 x 1032 x
+//     2512 (59) 722 / 753, 5 x 264 x 9832 (50) 667 / 693
+constexpr long kDownInOneBytes = 24l << 20;
 bool down_in_one(int K, int d, int d_ff, int dtype) {
   const int elem = dtype == 1 ? 2 : 4, step = kWave * (16 / elem);
-  return d_ff <= 4 * step || (long)K * d * d_ff * elem <= (d < 512 ? 24l : 64l) << 20;
+  return d_ff <= 4 * step || (long)K * d * d_ff * elem <= kDownInOneBytes;
 }
 
 template <int DT>
