@@ -623,12 +623,16 @@ __global__ __launch_bounds__(kPlanThreads) void prefill_plan_kernel(PlanArgs a) 
 // (eight layers in turn, where the host keeps ahead: 4 experts of d 1024 238 /
 // 231 us, 32 of d 256 268 / 253), with many experts more than the launch saves
 // (64 of d 256 44.2 / 42.4 and 330 / 297); one after the other they cost 48.7
-// and 364 there.  Rows of more than 2048 columns (two blocks': 1024) do not fit
+// and 364 there.  Rows of more than 2048 columns do not fit
 // the registers of a 1024-thread workgroup: held all the same they spill (16
 // tokens of 8 experts of d 4096 66.4 us), read again they cost more than the
-// launch saves (57.9 / 56.8; d 8192 89.8 / 87.9).
-constexpr bool route_plan_in_one(int blocks, int d, int E) {
-  return (blocks == 1 && d <= 2048) || (blocks == 2 && d <= 1024 && E <= 32);
+// launch saves (57.9 / 56.8; d 8192 89.8 / 87.9).  Two blocks of 1025 to 2048
+// columns cost 2 to 4 us more in one launch, which only pays where the experts
+// are so small that the host is behind (24 tokens: 4 experts of 1440 x 864, 28
+// MiB, 40.0 / 41.8; 8 of 2048 x 1024, 96 MiB, 49.2 / 46.9).
+constexpr bool route_plan_in_one(int blocks, int d, int E, uint64_t expert_bytes) {
+  return (blocks == 1 && d <= 2048) ||
+         (blocks == 2 && E <= 32 && (d <= 1024 || (d <= 2048 && E * expert_bytes <= (32u << 20))));
 }
 static_assert(kPlanThreads == kGateTok * kWave, "one workgroup does both");
 
@@ -898,12 +902,12 @@ hipError_t launch_prefill_gate(const PrefillArgs &a, const Launch &l) {
 
 hipError_t launch_prefill_route_plan(const PrefillArgs &a, const PlanArgs &p, const Launch &l) {
   const int blocks = (a.T + kGateTok - 1) / kGateTok;
-  if (route_plan_in_one(blocks, a.d, a.E)) {
+  if (route_plan_in_one(blocks, a.d, a.E, p.slot_bytes)) {
 #define MOE_ROUTE(NV, TB) MOE_LAUNCH((prefill_route_plan_kernel<NV, TB>), dim3(1), dim3(kPlanThreads), 0, l, a, p)
     if (blocks == 2 && a.d <= 512)
       MOE_ROUTE(2, 2);
     else if (blocks == 2)
-      MOE_ROUTE(4, 2);
+      MOE_ROUTE(4, 2);  // (columns past 1024 are read again: two rows of 2048 do not fit the registers)
     else if (a.d <= 512)
       MOE_ROUTE(2, 1);
     else if (a.d <= 1024)

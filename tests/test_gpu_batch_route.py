@@ -52,10 +52,12 @@ def test_one_block(d, T):
 
 
 @pytest.mark.parametrize("T", [17, 31, 32])
-@pytest.mark.parametrize("experts,d", [(20, 40), (32, 512), (20, 520), (32, 1024), (20, 1032), (33, 520)])
+@pytest.mark.parametrize("experts,d", [(20, 40), (32, 512), (20, 520), (32, 1024), (20, 1032), (20, 2048), (20, 2056),
+                                       (33, 520)])
 def test_two_blocks(experts, d, T):
-    # 17 to 32 tokens: one launch up to 1024 columns and 32 experts, a wave
-    # taking a token of each block (whole and partial second blocks)
+    # 17 to 32 tokens: one launch up to 1024 columns (2048 with experts as small
+    # as these) and 32 experts, a wave taking a token of each block (whole and
+    # partial second blocks)
     check(experts, 3, experts, d, T)
 
 
