@@ -119,29 +119,33 @@ constexpr int kWideRows = 256, kNarrowRows = 64;  // most rows of a wide and of 
 
 // How a launch's tiles are cut: column blocks of `cols` output columns, row
 // blocks of 32 * k rows with lo <= 32 * k <= hi (the plan chooses k), at most
-// `cap` tiles in all, `slots` of them at a time.
+// `cap` tiles in all, `slots` of them at a time.  staging: what a tile's weights
+// cost, in 32-row blocks.
 struct TileList {
   int cols, cb, lo, hi, first, cap, slots;
+  float staging;
 };
 
 // Relative cost of a launch whose experts are cut into `row_blocks` row blocks
 // of `blocks` 32-row blocks in all.  A tile costs its staging of the weights
-// (2.6 blocks' worth of wide tiles' 256 weight rows, 2 of narrow ones' 128) and
-// its blocks; a last round that fills only part of the chip costs half a round
-// and half its share.  Fitted on MI355X: wide to 2048 tokens of top-2 over 8
-// experts (down, d_ff 14336), rows a tile 96 .. 256: 592, 638, 538, 579, 615,
-// 622 us measured, 610, 638, 543, 574, 584, 635 by the model; narrow to which of
-// 32 and 64 rows a pass is faster with (us, 64 / 32): 4 experts of 2048 x 2048,
-// 96 tokens of top-2 66.5 / 53.1, 64 tokens 63.5 / 61.4; 64 of 512 x 256, 300
-// of top-8 50.1 / 47.0; 16 of 1024 x 1024, 192 of top-4 57.6 / 53.2; 12 of
-// 3072 x 1536, 200 of top-2 118.8 / 113.9; 8 of 4096 x 4096, 200 of top-1
-// 182.7 / 193.3; 8 of 4096 x 14336, 128 of top-2 495 / 567 (so chosen all seven).
+// (2.6 blocks' worth of wide tiles' 256 weight rows; of narrow ones' 128 rows 2
+// where they start on 128-byte lines, else 2.6) and its blocks; a last round
+// that fills only part of the chip costs half a round and half its share.
+// Fitted on MI355X: wide to 2048 tokens of top-2 over 8 experts (down, d_ff
+// 14336), rows a tile 96 .. 256: 592, 638, 538, 579, 615, 622 us measured, 610,
+// 638, 543, 574, 584, 635 by the model; narrow to which of 32 and 64 rows a pass
+// is faster with (us, 64 / 32): 4 experts of 2048 x 2048, 96 tokens of top-2
+// 66.5 / 53.1, 64 tokens 63.5 / 61.4; 64 of 512 x 256, 300 of top-8 50.1 / 47.0;
+// 16 of 1024 x 1024, 192 of top-4 57.6 / 53.2; 12 of 3072 x 1536, 200 of top-2
+// 118.8 / 113.9; 8 of 4096 x 4096, 200 of top-1 182.7 / 193.3; 8 of 4096 x 14336,
+// 128 of top-2 495 / 567; 17 of 1832 x 3248, 136 of top-4 190 / 202 (so chosen
+// all eight).
 __host__ __device__ inline float tile_cost(const TileList &t, int row_blocks, int blocks) {
   const int tiles = t.cb * row_blocks;
   if (tiles <= 0) return 0.0f;
-  const float n = (float)tiles / (float)t.slots, staging = t.hi == kNarrowRows ? 2.0f : 2.6f;
+  const float n = (float)tiles / (float)t.slots;
   const float rounds = 0.5f * ((float)((tiles + t.slots - 1) / t.slots) + n);
-  return rounds / n * (staging * (float)tiles + (float)(t.cb * blocks));
+  return rounds / n * (t.staging * (float)tiles + (float)(t.cb * blocks));
 }
 
 // Rows of an expert's tiles when its n > 0 rows are cut into blocks of at most

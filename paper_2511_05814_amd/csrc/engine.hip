@@ -912,7 +912,7 @@ static int device_cus(moe_cache *c) {
 // of d 2048 there are enough wide tiles and the two are equal).  The shortest
 // row blocks a plan may choose are those that a launch sized for any routing
 // can hold with at most two surplus workgroups a compute unit.
-static TileList tile_list(bool up, int ncols, long pairs, int experts, int cus, bool *wide) {
+static TileList tile_list(bool up, int ncols, int depth, long pairs, int experts, int cus, bool *wide) {
   const int wide_cols = prefill_tile_cols(up, true);
   *wide = (long)((ncols + wide_cols - 1) / wide_cols) * experts >= cus || pairs > 48L * experts;
   TileList t{};
@@ -920,6 +920,7 @@ static TileList tile_list(bool up, int ncols, long pairs, int experts, int cus, 
   t.cb = (ncols + t.cols - 1) / t.cols;
   t.hi = *wide ? kWideRows : kNarrowRows;
   t.slots = *wide ? cus : 2 * cus;
+  t.staging = *wide || depth % 64 != 0 ? 2.6f : 2.0f;
   // tiles of at most r rows: an expert with n > 0 rows has at most
   // 1 + (n - 1) / r of them per column block
   const long m = std::min<long>(experts, pairs);
@@ -1032,8 +1033,8 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
   bool up_wide = true, dn_wide = true, up_small = false, dn_small = false;
   if (on_device) {
     pa.tiles = tiles;
-    pa.up = tile_list(true, c->dff, pairs, c->E, cus, &up_wide);
-    pa.dn = tile_list(false, c->d, pairs, c->E, cus, &dn_wide);
+    pa.up = tile_list(true, c->dff, c->d, pairs, c->E, cus, &up_wide);
+    pa.dn = tile_list(false, c->d, c->dff, pairs, c->E, cus, &dn_wide);
     // experts that T tokens reach, routed evenly
     const double reached = c->E * (1.0 - std::pow(1.0 - (double)c->K / c->E, T));
     up_small = small_m(pa.up, up_wide, c->d, reached, (double)pairs, T, cus);
@@ -1184,8 +1185,8 @@ int prefill_enqueue(moe_cache *c, int layer, float *H, int T) {
       gr.rows += pl[e].n;
     }
     const int n = (int)group.size();
-    const TileList ul = tile_list(true, c->dff, gr.rows, n, cus, &gr.up.wide);
-    const TileList dl = tile_list(false, c->d, gr.rows, n, cus, &gr.dn.wide);
+    const TileList ul = tile_list(true, c->dff, c->d, gr.rows, n, cus, &gr.up.wide);
+    const TileList dl = tile_list(false, c->d, c->dff, gr.rows, n, cus, &gr.dn.wide);
     gr.up.small = small_m(ul, gr.up.wide, c->d, n, (double)gr.rows, gr.most, cus);
     gr.dn.small = small_m(dl, gr.dn.wide, c->dff, n, (double)gr.rows, gr.most, cus);
     const int small_first = nt;
