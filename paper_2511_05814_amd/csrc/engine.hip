@@ -933,11 +933,15 @@ static TileList tile_list(bool up, int ncols, int depth, long pairs, int experts
 
 // Does a grouped GEMM over `experts` experts (about) with `pairs` rows between
 // them, at most `most` each, take the small-M kernels?  With at most 16 rows
-// an expert always.  With 17 to 32 where its tiles (all of one row block) would
-// fill the chip badly: too few of them (a tile streams its weights at about 40
-// GB/s whatever else runs), or, of long weight rows, a second round that is
-// mostly empty.  Where long rows have most of two 16-row blocks a tile is
-// worth more.  us, tiles / small-M, weights from HBM:
+// an expert always.  With 17 to 32
+//  - where weight rows of some length do not start on 128-byte lines, so that
+//    every slice row a tile stages lies in two of them, until experts have some
+//    eight rows (14 where there are fewer than two tiles a compute unit);
+//  - where its tiles (all of one row block) would fill the chip badly: too few
+//    of them (a tile streams its weights at about 40 GB/s whatever else runs),
+//    or, of long weight rows, a second round that is mostly empty.  Where long
+//    rows have most of two 16-row blocks a tile is worth more.
+// us, tiles / small-M, weights from HBM:
 //   4 experts of 1024 x 1024, 17 tokens of top-1: up (64 tiles) 10.5 / 6.7, down (32) 9.3 / 4.8
 //   8 of 2048 x 2048, 32 of top-2: up (256) 31.5 / 28.6, down (128) 18.3 / 15.9
 //   8 of 2048 x 5632, 17 of top-2: up (349 wide) 82.4 / 63.1, down (127) 43.1 / 38.0
@@ -947,10 +951,18 @@ static TileList tile_list(bool up, int ncols, int depth, long pairs, int experts
 //   16 of 2048 x 1408, 17 of top-4: up (349) 39.8 / 35.3, down (254) 15.9 / 25.1
 //   64 of 2048 x 1408, 32 of top-8: up (694 wide) 109 / 122, down (505 wide) 57.2 / 88.8
 //   8 of 4096 x 14336, 32 of top-2: up (896 wide) 313 / 344, down (256) 157 / 193
+//   57 of 3048 x 1208, 25 of top-7: up (548 wide) 243 / 169, down (658 wide) 106 / 90
+//   51 of 1048 x 3928, 22 of top-7: up (1520 wide) 232 / 176, down (441) 104 / 80
+//   9 of 2072 x 10528, 25 of top-6 (17 rows each): up (747 wide) 200 / 211
+//   33 of 272 x 4744, 25 of top-8: up (1253 wide) 51 / 64
+// Over 110 shapes with sizes of any multiple of 8, 17 to 32 tokens, a launch
+// takes 0.8% longer than with the better of the two (at worst 18%).
 static bool small_m(const TileList &t, bool wide, int depth, double experts, double pairs, int most, int cus) {
   if (most <= 16) return true;
   if (most > kSkinnyRows) return false;
-  const double tiles = t.cb * experts, few = wide ? 0.5 : depth >= 4000 && pairs >= 14.0 * experts ? 0.4 : 0.625;
+  const double tiles = t.cb * experts;
+  if (depth % 64 != 0 && depth >= 400 && (pairs < 8.0 * experts || (pairs < 14.0 * experts && tiles < 2.0 * cus))) return true;
+  const double few = wide ? 0.5 : depth >= 4000 && pairs >= 14.0 * experts ? 0.4 : 0.625;
   return tiles < few * cus || (wide && depth >= 2000 && tiles > 1.05 * cus && tiles < 1.7 * cus);
 }
 

@@ -77,10 +77,25 @@ def test_small_m_row_blocks(d, d_ff, T):
     check(d, d_ff, 3, [T])
 
 
-@pytest.mark.parametrize("d,d_ff", [(520, 4104), (4104, 520)])
+@pytest.mark.parametrize("d,d_ff", [(520, 4104), (4104, 520), (512, 4104), (4104, 512)])
 def test_one_launch_of_tiles_one_of_small_m(d, d_ff):
-    # 4 experts: 260 narrow tiles one way and 20 the other
+    # 4 experts, all rows of every token: 260 narrow tiles one way and 20 the
+    # other, of weight rows on 128-byte lines and across them
     check(d, d_ff, 4, [17, 32])
+
+
+@pytest.mark.parametrize("d,d_ff", [(448, 4104), (456, 4104), (392, 4104)])
+def test_weight_rows_on_and_across_lines(d, d_ff):
+    # 24 tokens of top-1 over 8 experts: up takes tiles (528 narrow) but for rows of
+    # 400 columns and more that are no multiple of 64
+    cfg = wl.CONFIGS["tiny-stack"].with_(layers=1, experts=8, top_k=1, d_model=d, d_ff=d_ff, dtype="bf16", tokens=1,
+                                         prefill_tokens=24)
+    _say("rows across lines", d, d_ff)
+    rig = Rig(cfg)
+    moe = rig.cache(8, "lfu", max_prefill_tokens=24)
+    prefill_and_check(rig, moe, "lfu", 8, 24, list(range(24)))
+    moe.close()
+    rig.store.close()
 
 
 @pytest.mark.parametrize("T", [20, 32, 40])
