@@ -20,12 +20,12 @@
 // meet.  The loads are dealt out between the products, one every two to four:
 // issued back to back they fill the address path and stall the wave.
 //
-// Measured on MI355X (us, up / down): 4096 tokens of top-8 over 64 experts, d
-// 2048, d_ff 1408: 430 / 258 (eight waves of 64-row slabs, two slices, no
-// fragment prefetch: 423-489 / 249-270); 2048 tokens of top-2 over 8 experts,
-// d 4096, d_ff 14336: 915 / 515 (1011-1121 / 803-860).  Without its loads the
-// same loop takes 744 and without any operand traffic 686 of those 915, and
-// 76 of the 258 are the drain of the 268 MB result.
+// Measured on MI355X, us a launch in the trace (up / down, average of 12 in a row
+// and the fastest): 4096 tokens of top-8 over 64 experts, d 2048, d_ff 1408: 436 /
+// 268, 362 / 227; 2048 tokens of top-2 over 8 experts, d 4096, d_ff 14336: 1021 /
+// 592, 855 / 514.  A pass through each, against eight waves of 64-row slabs with two
+// slices and no fragment prefetch, in turn on one card: 784 -> 726 and 1877 ->
+// 1543.
 #include "common.hpp"
 
 #include <type_traits>
@@ -313,10 +313,10 @@ __device__ __forceinline__ void gemm_tile(const GemmTile &t, const uint16_t *a_s
 // different experts' do that faster.  Long lists are dealt in runs of as many
 // tiles as an XCD multiplies at once, so that every XCD gets its part of each
 // expert (tiles of different experts differ in height), with the last,
-// incomplete deal spread over all.  us with one stretch / runs of 32: 32 tokens
-// of top-8 over 64 experts 182 / 199, 509 tokens 240 / 248, 4096 tokens 693 /
-// 689, 2048 tokens of top-2 over 8 experts 1496 / 1467 (its down launch, of 480
-// tiles, in runs too).
+// incomplete deal spread over all.  us a pass with one stretch always / so /
+// runs from 256 tiles on: 32 tokens of top-8 over 64 experts 222 / 222 / 229, 509
+// tokens 253 / 252 / 277, 4096 tokens 735 / 722 / 720, 2048 tokens of top-2 over 8
+// experts 1518 / 1484 / 1473.
 constexpr int kXcds = 8, kXcdRun = 32, kLongList = 4 * kXcds * kXcdRun;
 
 __device__ __forceinline__ int xcd_tile(int b, int n) {
